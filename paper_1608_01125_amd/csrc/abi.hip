@@ -75,6 +75,12 @@ constexpr int64_t kBatchBudget = (int64_t)1 << 27;  // default virtual elements 
 // scratch each) so that a launch still covers kBatchStepsMin steps
 constexpr int64_t kBatchBudgetMax = (int64_t)1 << 29;
 constexpr int64_t kBatchStepsMin = 32;
+// steps per window of the cloud traversal: shorter windows meet a pair again and again (a
+// pair's clouds overlap for 12 to 44 steps in the statistical workloads), longer ones reach
+// pairs that never overlap and leave fewer waves. Training rows of 2e4 clouds per beam and the
+// audit of 2e5: 17.4 and 43.8 ms at 4 steps, 13.0 and 32.4 at 8, 11.0 and 26.8 at 16, 11.3
+// and 27.9 at 32, 12.6 and 29.3 at 64.
+constexpr int64_t kStWin = 16;
 // with window copies (the plain regime) a launch's tree buffers hold a copy per window, not
 // per step, and its query buffers one record per row: every beam takes up to kBatchBudgetMax
 // virtual elements per launch (the whole 400-step run of two 1e6-photon beams in one launch,
@@ -119,7 +125,11 @@ struct tril_ctx {
     bool ad_quad = false;           // a tril_run since then descended four-child forms
     int morton_param = 0;           // Morton bits requested (0 = automatic)
     CloudBox cloud{0, {0.0, 0.0, 0.0}};  // box kind of the builds (statistical regime: clouds)
+    double box_dt = 0.0;            // time one box covers: dt, or a window of the statistical
+    int32_t box_steps = 0;          // regime; the steps its launch covers (0: one per box)
     double *st_slots = nullptr;     // statistical regime: per-wave yield sums (kCounterSlots)
+    StRec *st_qrec = nullptr, *st_trec = nullptr;  // the cloud traversal's photon records
+    int64_t st_qrec_cap = 0, st_trec_cap = 0;
     // surrogate path scratch: bin clouds, bin-pair overlap table, features, exact fallback
     WorkBeam sr_q, sr_t;
     int32_t *sr_q_bin = nullptr, *sr_t_bin = nullptr;
@@ -195,6 +205,7 @@ struct tril_ctx {
     int64_t n_int = -1;                    // internal nodes of the last build (all steps)
     int32_t tgt_k0 = 0;                    // first step of the last build
     CloudBox tgt_cloud{0, {0.0, 0.0, 0.0}};  // box kind of the last build
+    double tgt_dt = 0.0;                     // time one box of the last build covers
 
     // query state
     int64_t q_cap = 0, q_row_cap = 0;
@@ -602,9 +613,9 @@ int enqueue_build(tril_ctx *c, hipStream_t st, bool timed, bool presorted = fals
     c->win_eff = win;
     const KeyLayout kl = key_layout(t.n_inst, c->morton_bits);
     if (timed) CHK(timing_pair(c, st, c->ev_build, true));
-    launch_prologue(c->d_cnt, 0, t.m, st);
+    launch_prologue(c->d_cnt, 0, c->box_steps > 0 ? c->box_steps : t.m, st);
     // sort keys only: the refit forms every step's leaf boxes from the photons itself
-    launch_boxes_keys(t, false, c->cloud, c->dt, c->sigma_up, c->t_stats, c->t_stats, kl,
+    launch_boxes_keys(t, false, c->cloud, c->box_dt, c->sigma_up, c->t_stats, c->t_stats, kl,
                       key_step(t.m), nullptr, c->t_k32a, c->t_k64a, c->t_va, c->d_cnt, st);
     const uint32_t *rows = nullptr;
     int32_t *roots = t.n_inst > 1 ? c->inst_base : nullptr;
@@ -625,10 +636,11 @@ int enqueue_build(tril_ctx *c, hipStream_t st, bool timed, bool presorted = fals
     c->t_rows = rows;
     c->n_int = n > 0 ? (int64_t)copies * (n - 1) : -1;
     c->tgt_cloud = c->cloud;
+    c->tgt_dt = c->box_dt;
     if (win > 1) launch_win_bounds(c->t_stats, t.n_inst, c->dt, c->t_wb, st);
     c->quad = win > 1 && n > 1 && (int64_t)copies * (n - 1) <= c->nodes4_cap &&
               copies <= c->frames_cap && n - 1 <= c->inside_cap;
-    launch_inst_roots(t, c->cloud, c->dt, c->inst_base, rows, c->inst_root, c->root_box, c->d_cnt,
+    launch_inst_roots(t, c->cloud, c->box_dt, c->inst_base, rows, c->inst_root, c->root_box, c->d_cnt,
                       st, win, c->t_rec);
     int32_t *xbase = nullptr;
     bool xalt = false;
@@ -639,7 +651,7 @@ int enqueue_build(tril_ctx *c, hipStream_t st, bool timed, bool presorted = fals
     // four-child forms: the frames first; the refit forms the nodes whose descendants lie in
     // one of its chunks, the collapse the others
     if (c->quad) launch_win_frames(c->t_stats, t.n_inst, c->dt, win, t.m, c->d_cnt, c->t_frames, st);
-    launch_refit(t, c->cloud, c->dt, rows, c->prec, c->nflags, c->nodes, c->refit_slots,
+    launch_refit(t, c->cloud, c->box_dt, rows, c->prec, c->nflags, c->nodes, c->refit_slots,
                  c->refit_slot_cap, xbase, xalt, c->d_cnt, &c->d_cnt->err, st, win, c->t_rec,
                  c->quad ? c->t_frames : nullptr, c->quad ? c->nodes4 : nullptr,
                  c->quad ? c->t_inside : nullptr, c->keep_nodes);
@@ -659,7 +671,7 @@ int enqueue_query_prep(tril_ctx *c, const BeamDev &q, hipStream_t st, bool sort_
                        bool records = false, SortScratch *ss = nullptr) {
     SortScratch &sq = ss != nullptr ? *ss : c->ss;
     const KeyLayout kl = key_layout(q.n_inst, c->morton_bits);
-    launch_boxes_keys(q, true, c->cloud, c->dt, c->sigma_up, c->t_stats, c->q_stats, kl,
+    launch_boxes_keys(q, true, c->cloud, c->box_dt, c->sigma_up, c->t_stats, c->q_stats, kl,
                       key_step(q.m), records ? nullptr : c->q_box, c->q_k32a, c->q_k64a, c->q_va,
                       c->d_cnt, st, records ? c->q_rec : nullptr);
     if (sort_queries && q.n > 0 && q.m > 0) {
@@ -1026,6 +1038,8 @@ int tril_create(tril_ctx **out, const tril_params *p, void *stream) {
     tril_ctx *c = new tril_ctx();
     c->st = reinterpret_cast<hipStream_t>(stream);
     c->dt = p->dt;
+    c->box_dt = p->dt;
+    c->tgt_dt = p->dt;
     c->flags = p->flags;
     c->n_bins = p->n_bins;
     c->cand_cap_param = p->cand_cap;
@@ -1408,7 +1422,8 @@ int tril_stats(tril_ctx *c, tril_pairs *p, tril_stats_t *out) {
     if (p) HIPCHK(hipMemcpyAsync(hp, p->count, sizeof(int64_t), hipMemcpyDeviceToHost, c->st));
     HIPCHK(hipStreamSynchronize(c->st));
     const DevCounters &h = *c->h_cnt;
-    out->n_candidates = (int64_t)h.cand_total + (int64_t)h.st_pairs;
+    out->n_candidates = (int64_t)h.cand_total;
+    for (int s = 0; s < kCounterSlots; ++s) out->n_candidates += (int64_t)h.st_pairs[s];
     int64_t visits = 0, queries = 0, checks = 0;
     for (int k = 0; k < kCounterSlots; ++k) {
         visits += (int64_t)h.visits[k];
@@ -1582,19 +1597,39 @@ int tril_st_bin(const tril_beam *b, const tril_st_grid *g, int32_t *bins, double
 
 namespace {
 
+int ensure_st_rec(tril_ctx *c, StRec *&rec, int64_t &cap, int64_t n) {
+    if (n <= cap) return TRIL_OK;
+    dev_free(rec);
+    cap = 0;
+    CHK(dev_alloc(&rec, (size_t)n));
+    cap = n;
+    return TRIL_OK;
+}
+
 // Statistical-regime pass over steps k0 .. k0+n_steps-1 (asynchronous): clouds of edges
-// `cell` in a hierarchy per step, yields (or, geometric, overlap integrals) added to the
-// table under (q_bins[i], t_bins[j]); with a filter set, only its keys. Per-wave sums go
-// to c->st_slots (cleared here together with the table).
+// `cell` in a hierarchy per window of steps, yields (or by `mode` overlap integrals,
+// exposures, meetings) added to the table under (q_bins[i], t_bins[j]) or the cloud pair;
+// with a filter set, only its keys. Per-wave sums go to c->st_slots (cleared here together
+// with the table).
 int st_run(tril_ctx *c, const tril_beam *t, const int32_t *t_bins, int64_t n_t_bins,
            const tril_beam *q, const int32_t *q_bins, const double cell[3], int32_t k0,
-           int32_t n_steps, int geometric, const long long *filter, int64_t filter_cap,
+           int32_t n_steps, int mode, const long long *filter, int64_t filter_cap,
            long long *keys, double *vals, int64_t cap) {
     if (!c->st_slots) CHK(dev_alloc(&c->st_slots, (size_t)kCounterSlots));
     launch_st_clear(keys, vals, cap, c->st_slots, c->st);
-    const int32_t m = n_steps > 0 ? pick_batch(c, t, q, n_steps) : 1;
+    const int32_t ms = n_steps > 0 ? pick_batch(c, t, q, n_steps) : 1;
+    // swarms (mode 3) keep a descent per step: their pairs are those whose clouds, swept over
+    // one step, meet
+    const int32_t win =
+        mode == 3 ? 1 : (int32_t)std::max<int64_t>(1, std::min<int64_t>(kStWin, std::min(n_steps, ms)));
+    // windows are aligned to multiples of their length; the first and the last may be cut
+    const int64_t kw0 = k0 / win;
+    const int64_t n_win = n_steps > 0 ? (k0 + (int64_t)n_steps - 1) / win - kw0 + 1 : 0;
+    const int32_t m = (int32_t)std::max<int64_t>(1, std::min<int64_t>(n_win, ms / win));
     CHK(ensure_target(c, (int64_t)m * t->n, t->n, (int64_t)m * t->n_inst, t->n_inst));
     CHK(ensure_query(c, (int64_t)m * q->n, q->n, (int64_t)m * q->n_inst, q->n_inst));
+    CHK(ensure_st_rec(c, c->st_qrec, c->st_qrec_cap, q->n));
+    CHK(ensure_st_rec(c, c->st_trec, c->st_trec_cap, t->n));
     CHK(upload_offsets(c, t, c->d_t_off, c->h_t_off));
     CHK(upload_offsets(c, q, c->d_q_off, c->h_q_off));
     c->nt = t->n;
@@ -1602,31 +1637,38 @@ int st_run(tril_ctx *c, const tril_beam *t, const int32_t *t_bins, int64_t n_t_b
     const BeamDev t1 = view(t, c->d_t_off, 1), q1 = view(q, c->d_q_off, 1);
     // caller photons must be light-like; the bin clouds of the surrogate's geometric pass
     // (mode 1) carry mean directions
-    launch_beam_stats(t1, c->t_spart, c->t_stats, c->d_cnt, c->st, geometric != 1);
-    launch_beam_stats(q1, c->q_spart, c->q_stats, c->d_cnt, c->st, geometric != 1);
+    launch_beam_stats(t1, c->t_spart, c->t_stats, c->d_cnt, c->st, mode != 1);
+    launch_beam_stats(q1, c->q_spart, c->q_stats, c->d_cnt, c->st, mode != 1);
+    launch_st_pack(t1, t_bins, c->st_trec, c->st);
+    launch_st_pack(q1, q_bins, c->st_qrec, c->st);
     const StCell sc{{cell[0], cell[1], cell[2]}};
-    // clouds at mid-step; swarms (geometric 3): clouds swept over the step
-    c->cloud = CloudBox{geometric == 3 ? 2 : 1, {0.5 * cell[0], 0.5 * cell[1], 0.5 * cell[2]}};
+    // clouds swept over a window (swarms: over a step)
+    c->cloud = CloudBox{1, {0.5 * cell[0], 0.5 * cell[1], 0.5 * cell[2]}};
+    c->box_dt = (double)win * c->dt;
     c->morton_bits = c->morton_param > 0 ? c->morton_param : 30;
     int rc = TRIL_OK;
-    for (int32_t k = k0, left = n_steps; left > 0 && rc == TRIL_OK;) {
-        const int32_t mb = std::min(m, left);
+    for (int64_t kw = kw0, left = n_win; left > 0 && rc == TRIL_OK;) {
+        const int32_t mb = (int32_t)std::min<int64_t>(m, left);
+        const int64_t ka = std::max<int64_t>(k0, kw * win);
+        const int64_t kb = std::min<int64_t>((int64_t)k0 + n_steps, (kw + mb) * win);
+        c->box_steps = (int32_t)(kb - ka);
         c->tgt = view(t, c->d_t_off, mb);
         const BeamDev qv = view(q, c->d_q_off, mb);
-        launch_set_step(c->d_cnt, k, c->st);
-        c->tgt_k0 = k;
+        launch_set_step(c->d_cnt, (int32_t)kw, c->st);
+        c->tgt_k0 = (int32_t)ka;
         if ((rc = enqueue_build(c, c->st, false)) != TRIL_OK) break;
-        launch_prologue(c->d_cnt, 1, mb, c->st);
+        launch_prologue(c->d_cnt, 1, c->box_steps, c->st);
         if ((rc = enqueue_query_prep(c, qv, c->st, true)) != TRIL_OK) break;
-        const int64_t nqv = (int64_t)mb * q->n;
-        launch_st_traverse(c->nodes, c->n_int, c->root_box, c->q_box, nqv > 0 ? c->q_order : nullptr,
-                           c->q_order_len, nqv, q->n, c->inst_root, qv, c->tgt, q_bins, t_bins,
-                           n_t_bins, c->dt, sc, geometric, filter, filter_cap, keys, vals, cap,
+        launch_st_traverse(c->nodes, c->n_int, c->root_box, c->q_box, c->q_order, q->n, mb,
+                           c->inst_root, t->n, c->st_qrec, c->st_trec, n_t_bins, c->dt, win, k0,
+                           k0 + n_steps - 1, sc, mode, filter, filter_cap, keys, vals, cap,
                            c->st_slots, c->d_cnt, c->st);
-        k += mb;
+        kw += mb;
         left -= mb;
     }
     c->cloud.on = 0;
+    c->box_dt = c->dt;
+    c->box_steps = 0;
     CHK(rc);
     HIPCHK(hipGetLastError());
     c->built = true;
@@ -2761,7 +2803,7 @@ void tril_destroy(tril_ctx *c) {
         free_work(c->wt[p]);
         free_work(c->wq[p]);
     }
-    dev_free(c->st_slots);
+    dev_free(c->st_slots); dev_free(c->st_qrec); dev_free(c->st_trec);
     free_work(c->sr_q); free_work(c->sr_t);
     dev_free(c->sr_q_bin); dev_free(c->sr_t_bin);
     dev_free(c->sg_key); dev_free(c->sg_val);
@@ -2994,7 +3036,7 @@ int tril_dbg_boxes(tril_ctx *c, int which, void *boxes, int64_t cap, int64_t *n)
                 src = tmp;
             }
             launch_set_step(c->d_cnt, c->tgt_k0, c->st);
-            launch_leaf_boxes(c->tgt, c->tgt_cloud, c->dt, c->d_cnt, src, c->st);
+            launch_leaf_boxes(c->tgt, c->tgt_cloud, c->tgt_dt, c->d_cnt, src, c->st);
             const hipError_t e = hipGetLastError();
             const hipError_t e2 = hipStreamSynchronize(c->st);
             if (e != hipSuccess || e2 != hipSuccess) {

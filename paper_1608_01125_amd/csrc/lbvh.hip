@@ -319,10 +319,11 @@ __device__ __forceinline__ RowPhoton load_photon(const BeamDev &b, int64_t i, do
 
 // Box of photon r in the step window [t, t + dt], padded by pad and rounded outward to
 // FP32, and its centre: the swept segment (position at t exactly as the narrow phase
-// forms it, and one step later); in the statistical regime (cloud.on == 1) the cloud
-// (half-widths cloud.h about the mid-step position); for swarms (cloud.on == 2) the cloud
-// swept over the step (the segment's box widened by cloud.h). A photon with unusable data
-// gets an empty box.
+// forms it, and one step later); in the statistical regime (cloud.on) the cloud swept over
+// the window (the segment's box widened by the cloud's half-widths cloud.h), which holds the
+// cloud of every mid-step in it: those lie half a step inside the segment's ends, and where
+// a photon hardly moves along an axis the slack below covers the rounding of its positions.
+// A photon with unusable data gets an empty box.
 __device__ __forceinline__ void photon_box(const RowPhoton &r, double t, double dt,
                                            const CloudBox &cloud, double pad, float lo32[3],
                                            float hi32[3], float cen[3]) {
@@ -336,22 +337,15 @@ __device__ __forceinline__ void photon_box(const RowPhoton &r, double t, double 
         return;
     }
     double lo[3], hi[3];
-    if (cloud.on == 1) {
-        const double tm = t + 0.5 * dt;
-        const double cx = r.x + tm * r.ux, cy = r.y + tm * r.uy, cz = r.z + tm * r.uz;
-        lo[0] = cx - cloud.h[0]; lo[1] = cy - cloud.h[1]; lo[2] = cz - cloud.h[2];
-        hi[0] = cx + cloud.h[0]; hi[1] = cy + cloud.h[1]; hi[2] = cz + cloud.h[2];
-    } else {
-        const double ax = r.x + t * r.ux, ay = r.y + t * r.uy, az = r.z + t * r.uz;
-        const double bx = ax + dt * r.ux, by = ay + dt * r.uy, bz = az + dt * r.uz;
-        lo[0] = fmin(ax, bx); lo[1] = fmin(ay, by); lo[2] = fmin(az, bz);
-        hi[0] = fmax(ax, bx); hi[1] = fmax(ay, by); hi[2] = fmax(az, bz);
-        if (cloud.on == 2) {
+    const double ax = r.x + t * r.ux, ay = r.y + t * r.uy, az = r.z + t * r.uz;
+    const double bx = ax + dt * r.ux, by = ay + dt * r.uy, bz = az + dt * r.uz;
+    lo[0] = fmin(ax, bx); lo[1] = fmin(ay, by); lo[2] = fmin(az, bz);
+    hi[0] = fmax(ax, bx); hi[1] = fmax(ay, by); hi[2] = fmax(az, bz);
+    if (cloud.on) {
 #pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                lo[a] -= cloud.h[a];
-                hi[a] += cloud.h[a];
-            }
+        for (int a = 0; a < 3; ++a) {
+            lo[a] -= cloud.h[a];
+            hi[a] += cloud.h[a];
         }
     }
     // slack far above FP64 rounding of the positions (1e-12 of the magnitude)
@@ -395,14 +389,14 @@ __global__ void __launch_bounds__(256) k_boxes_keys(BeamDev b, int query, CloudB
     const RowPhoton r = load_photon(b, i, E, w);
     double pad = 0.0;
     bool below = false;
-    if (query && r.ok) {  // (the cloud regime needs no radius pad: clouds overlap or not)
+    if (query && r.ok) {
         const InstStats &ts = t_stats[mi];
         const double emax_t = __longlong_as_double((long long)ts.emax);
         const double wmax_t = __longlong_as_double((long long)ts.wmax);
         const double smax = (E * emax_t) / (kMe * kMe);
         below = !(smax > 1.0);
         if (!cloud.on) pad = sqrt((sqrt(w * wmax_t) * sigma_up) / M_PI) * (1.0 + 1e-6);
-        if (cloud.on == 2) pad = sqrt(sigma_up / M_PI) * (1.0 + 1e-6);  // real photons, weight 1
+        else pad = sqrt(sigma_up / M_PI) * (1.0 + 1e-6);  // swarms: real photons, weight 1
     }
     const unsigned step0 = c->step;
     if (rec != nullptr) {  // the batch's record of the row: its box at offset 0, moved per step

@@ -114,24 +114,43 @@ __device__ __forceinline__ uint64_t mix64(uint64_t k) {
 // holds its keys at moderate load never gets near it.
 constexpr uint64_t kMaxProbe = 1024;
 
-__device__ void table_add(long long *keys, double *vals, uint64_t mask, long long key, double v,
-                          unsigned int *err) {
+// Adds v under key. The slots of a probe are read kProbe at a time: a wave waits for the longest
+// probe of its 64 lanes, about 20 slots at a load of 0.6, and each slot read by itself is a
+// round trip to memory (the cloud traversal took 2.5 ms per exact pass of 2e4 clouds per beam
+// that way). The reads may be stale: a slot's key never changes once it is set, so a key that
+// is seen is there, and an empty slot is claimed by the compare-and-swap, which sees the truth.
+constexpr int kProbe = 8;
+__device__ __forceinline__ void table_add(long long *keys, double *vals, uint64_t mask,
+                                          long long key, double v, unsigned int *err) {
     uint64_t h = mix64((uint64_t)key) & mask;
-    for (uint64_t probe = 0; probe <= mask && probe < kMaxProbe; ++probe) {
-        const long long cur = __hip_atomic_load(keys + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (cur == key) {
-            atomicAdd(vals + h, v);
-            return;
-        }
-        if (cur == -1ll) {
-            const long long prev = (long long)atomicCAS(
-                reinterpret_cast<unsigned long long *>(keys + h), ~0ull, (unsigned long long)key);
+    for (uint64_t probe = 0; probe <= mask && probe < kMaxProbe; probe += kProbe) {
+        long long cur[kProbe];
+#pragma unroll
+        for (int r = 0; r < kProbe; ++r) cur[r] = keys[(h + r) & mask];
+        int at = kProbe;  // first slot that holds the key or is free
+#pragma unroll
+        for (int r = kProbe - 1; r >= 0; --r)
+            if (cur[r] == key || cur[r] == -1ll) at = r;
+        while (at < kProbe) {
+            const uint64_t slot = (h + at) & mask;
+            long long prev = key;
+            bool known = false;
+#pragma unroll
+            for (int r = 0; r < kProbe; ++r) known |= r == at && cur[r] == key;
+            if (!known)
+                prev = (long long)atomicCAS(reinterpret_cast<unsigned long long *>(keys + slot),
+                                            ~0ull, (unsigned long long)key);
             if (prev == -1ll || prev == key) {
-                atomicAdd(vals + h, v);
+                atomicAdd(vals + slot, v);
                 return;
             }
+            int next = kProbe;  // taken meanwhile: the next candidate of this batch
+#pragma unroll
+            for (int r = kProbe - 1; r >= 0; --r)
+                if (r > at && (cur[r] == key || cur[r] == -1ll)) next = r;
+            at = next;
         }
-        h = (h + 1) & mask;
+        h = (h + kProbe) & mask;
     }
     atomicOr(err, kErrTableFull);
 }
@@ -147,56 +166,127 @@ __device__ __forceinline__ bool set_has(const long long *keys, uint64_t mask, lo
     return false;
 }
 
-// Y_ij,k of one cloud pair (see the file comment), FP64 (geometric = 1: dt V_ov only, the
-// clouds' overlap integrated over the step; pairs at or below threshold still give nothing).
-__device__ __forceinline__ double st_yield(const BeamDev &q, int64_t i, const BeamDev &t, int64_t j,
-                                           double tk, double dt, const StCell &cell, int geometric) {
-    const double Ei = q.E[i], Ej = t.E[j];
-    const double uix = q.px[i] / Ei, uiy = q.py[i] / Ei, uiz = q.pz[i] / Ei;
-    const double ujx = t.px[j] / Ej, ujy = t.py[j] / Ej, ujz = t.pz[j] / Ej;
-    const double cphi = (uix * ujx + uiy * ujy) + uiz * ujz;
-    const double s = ((Ei * Ej) * (1.0 - cphi)) / (2.0 * kMe * kMe);
-    if (!(s > 1.0)) return 0.0;
-    if (geometric == 3) return 1.0;  // swarms: the swept clouds meet, above threshold
-    const double tm = tk + 0.5 * dt;
-    const double ox = cell.c[0] - fabs((q.x[i] + tm * uix) - (t.x[j] + tm * ujx));
-    const double oy = cell.c[1] - fabs((q.y[i] + tm * uiy) - (t.y[j] + tm * ujy));
-    const double oz = cell.c[2] - fabs((q.z[i] + tm * uiz) - (t.z[j] + tm * ujz));
-    if (!(ox > 0.0 && oy > 0.0 && oz > 0.0)) return 0.0;
-    const double vov = (ox * oy) * oz;
-    if (geometric == 1) return dt * vov;
-    const double V = (cell.c[0] * cell.c[1]) * cell.c[2];
-    if (geometric == 2) return (((bw_sigma(s) * (1.0 - cphi)) * dt) * vov) / V;
-    return (((((q.w[i] * t.w[j]) / (V * V)) * bw_sigma(s)) * (1.0 - cphi)) * dt) * vov;
+// One photon as the cloud traversal reads it: its position at t = 0, direction p / E, energy,
+// weight and bin, in one 80-B record (the pair test would gather ten scattered words, and
+// divide, from the beam's arrays).
+__global__ void __launch_bounds__(256) k_st_pack(BeamDev b, const int32_t *__restrict__ bins,
+                                                 StRec *__restrict__ rec) {
+    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (i >= b.n) return;
+    const double E = b.E[i];
+    StRec r;
+    r.x[0] = b.x[i]; r.x[1] = b.y[i]; r.x[2] = b.z[i];
+    r.u[0] = b.px[i] / E; r.u[1] = b.py[i] / E; r.u[2] = b.pz[i] / E;
+    r.E = E;
+    r.w = b.w[i];
+    r.bin = bins[i];
+    r.pad = 0;
+    rec[i] = r;
 }
 
-// One overlapping leaf of the cloud traversal: the pair's yield, accumulated per run
-// of equal bin-pair keys (consecutive leaves of a query mostly share a target bin).
-__device__ __forceinline__ void st_leaf(const BeamDev &q, int64_t i, const BeamDev &t, int64_t e,
-                                        int64_t so, double tk, double dt, const StCell &cell,
-                                        int geometric, int32_t bq,
-                                        const int32_t *__restrict__ t_bins, int64_t n_t_bins,
-                                        const long long *__restrict__ filter, uint64_t fmask,
-                                        long long *keys, double *vals, uint64_t mask,
-                                        long long &cur_key, double &acc, double &lane_total,
-                                        uint32_t &n_pairs, DevCounters *c) {
-    const int64_t j = e - so * t.n;
-    const int32_t bt = t_bins[j];
-    // bin-pair key, or in exposure mode the cloud pair (caller rows)
-    const long long key = geometric >= 2 ? (long long)i * t.n + j : (long long)bq * n_t_bins + bt;
-    const bool keep = bt >= 0 && (filter == nullptr || set_has(filter, fmask, key));
-    const double Y = keep ? st_yield(q, i, t, j, tk, dt, cell, geometric) : 0.0;
-    if (Y > 0.0) {
-        ++n_pairs;
-        lane_total += Y;
-        if (key != cur_key) {
-            if (cur_key >= 0) table_add(keys, vals, mask, cur_key, acc, &c->err);
-            cur_key = key;
-            acc = Y;
-        } else {
-            acc += Y;
-        }
+// What the cloud traversal adds per overlapping pair and step.
+enum : int { kStYield = 0, kStOverlap = 1, kStExposure = 2, kStMeet = 3 };
+
+// First and last step (clamped to [k0, k1]) in which two clouds at distance d + t v (per
+// axis, t the mid-step time) can overlap along one axis of edge c; sl is far above the FP64
+// rounding of the positions, so no overlapping step falls outside. The quotients are those of
+// a refined reciprocal: their error, relative 1e-15, is covered by the rounding outward to
+// whole steps.
+__device__ __forceinline__ void axis_steps(double d, double v, double c, double sl, double t_end,
+                                           double inv_dt, double &lo, double &hi) {
+    const double h = c + sl;
+    if (fabs(v) * t_end <= 0.5 * sl) {  // no motion beyond the slack: all steps or none
+        if (fabs(d) > h) lo = INFINITY;
+        return;
     }
+    double r = __builtin_amdgcn_rcp(v);
+    r = r * (2.0 - v * r);
+    r = r * (2.0 - v * r);
+    const double t1 = (-h - d) * r, t2 = (h - d) * r;
+    lo = fmax(lo, floor(fmin(t1, t2) * inv_dt - 0.5));
+    hi = fmin(hi, ceil(fmax(t1, t2) * inv_dt - 0.5));
+}
+
+// The cross-section as bw_sigma's formula has it, with one reciprocal of s and, well above
+// threshold, one logarithm: 2 log1p(b) + ln s = ln((1 + b)^2 s), whose rounded argument costs
+// an absolute 3e-16 of a logarithm above 1 (closer to threshold the two logarithms stay).
+__device__ __forceinline__ double st_sigma(double s) {
+    if (!(s > 2.0)) return bw_sigma(s);
+    const double r = 1.0 / s;
+    const double b2 = (s - 1.0) * r;
+    const double b = sqrt(b2);
+    const double L = log(((1.0 + b) * (1.0 + b)) * s);
+    return (((0.5 * M_PI) * (kRe * kRe)) * r) * ((3.0 - b2 * b2) * L - (2.0 * b) * (2.0 - b2));
+}
+
+// One query photon and leaf whose hulls met: the sum over the steps of [k0, k1] in which the
+// two clouds overlap, under its key (-1: nothing). Pair quantities (s, sigma, 1 - u_i.u_j, the weights) do not depend on the step and are
+// formed once. cnt: the steps with a positive value.
+__device__ __forceinline__ long long st_pair(const StRec &q, int64_t i, int32_t k0, int32_t k1,
+                                             const StRec *__restrict__ trec, int64_t j, int64_t n_t,
+                                             double dt, double inv_dt, double inv_vv,
+                                             const StCell &cell, int mode, int64_t n_t_bins,
+                                             const long long *__restrict__ filter, uint64_t fmask,
+                                             double &sum, uint32_t &cnt) {
+    sum = 0.0;
+    cnt = 0;
+    const StRec t = trec[j];
+    if (t.bin < 0) return -1ll;
+    // bin-pair key, or in exposure and swarm mode the cloud pair (caller rows)
+    const long long key = mode >= kStExposure ? (long long)i * n_t + j
+                                              : (long long)q.bin * n_t_bins + t.bin;
+    if (filter != nullptr && !set_has(filter, fmask, key)) return -1ll;
+    const double cphi = (q.u[0] * t.u[0] + q.u[1] * t.u[1]) + q.u[2] * t.u[2];
+    const double s = ((q.E * t.E) * (1.0 - cphi)) / (2.0 * kMe * kMe);
+    if (!(s > 1.0)) return -1ll;
+    if (mode == kStMeet) {  // swarms: the swept clouds meet, above threshold
+        sum = 1.0;
+        cnt = 1;
+        return key;
+    }
+    const double t_end = ((double)k1 + 1.0) * dt;
+    double lo = (double)k0, hi = (double)k1;
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+        axis_steps(q.x[a] - t.x[a], q.u[a] - t.u[a], cell.c[a],
+                   1e-11 * (1.0 + fabs(q.x[a]) + fabs(t.x[a]) + t_end), t_end, inv_dt, lo, hi);
+    if (!(lo <= hi)) return -1ll;
+    const double V = (cell.c[0] * cell.c[1]) * cell.c[2];
+    double f = dt;
+    if (mode == kStYield)
+        f = (((q.w * t.w) * inv_vv) * st_sigma(s)) * (1.0 - cphi) * dt;
+    else if (mode == kStExposure)
+        f = (st_sigma(s) * (1.0 - cphi)) * dt / V;
+    // The overlap along each axis from the pair's distance. The definition takes it from the
+    // two positions, whose rounding is below 4e-16 of their magnitude: an overlap of more than
+    // 1e-5 of that magnitude differs by less than 1e-10 of itself, a smaller one is formed,
+    // and the step decided, as the definition has it.
+    const double d0 = q.x[0] - t.x[0], d1 = q.x[1] - t.x[1], d2 = q.x[2] - t.x[2];
+    const double v0 = q.u[0] - t.u[0], v1 = q.u[1] - t.u[1], v2 = q.u[2] - t.u[2];
+    const double near = 1e-5 * (1.0 + fmax(fmax(fabs(q.x[0]) + fabs(t.x[0]), fabs(q.x[1]) + fabs(t.x[1])),
+                                            fabs(q.x[2]) + fabs(t.x[2])) + t_end);
+    const int32_t ka = (int32_t)lo, steps = (int32_t)(hi - lo);
+    double vol = 0.0;
+    for (int32_t r = 0; r <= steps; ++r) {
+        const double tm = (double)(ka + r) * dt + 0.5 * dt;
+        double ox = cell.c[0] - fabs(fma(tm, v0, d0));
+        double oy = cell.c[1] - fabs(fma(tm, v1, d1));
+        double oz = cell.c[2] - fabs(fma(tm, v2, d2));
+        const double o = fmin(fmin(ox, oy), oz);
+        if (fabs(o) <= near) {
+            ox = cell.c[0] - fabs((q.x[0] + tm * q.u[0]) - (t.x[0] + tm * t.u[0]));
+            oy = cell.c[1] - fabs((q.x[1] + tm * q.u[1]) - (t.x[1] + tm * t.u[1]));
+            oz = cell.c[2] - fabs((q.x[2] + tm * q.u[2]) - (t.x[2] + tm * t.u[2]));
+            if (!(ox > 0.0 && oy > 0.0 && oz > 0.0)) continue;
+        } else if (!(o > 0.0)) {
+            continue;
+        }
+        const double vov = (ox * oy) * oz;
+        vol += vov;
+        if (f * vov > 0.0) ++cnt;
+    }
+    sum = f * vol;
+    return cnt > 0 ? key : -1ll;
 }
 
 __device__ __forceinline__ bool st_overlap(const float q[6], float4 lo, float4 hi) {
@@ -204,104 +294,207 @@ __device__ __forceinline__ bool st_overlap(const float q[6], float4 lo, float4 h
            (q[5] >= lo.z);
 }
 
-constexpr int kStStack = 128;  // deeper than any radix tree over (key, index) pairs
+constexpr int kStQueries = 16;  // query photons of one wave
+constexpr int kStStack = 1024;  // pending nodes of a wave
+constexpr int kStDepth = 128;   // deeper than any radix tree over (key, index) pairs
 
-// Descent as in the broad phase of the exact regime (one load per overlapped internal
-// node, both children tested from it, pending right children on a per-lane stack).
-template <int BLOCK>
-__global__ void __launch_bounds__(BLOCK) k_st_traverse(
+// Cloud traversal: one wave per kStQueries neighbouring query photons (in Morton order) and
+// window of win consecutive steps. The boxes hold the clouds swept over the window, so one
+// descent reaches every pair that overlaps in any of its steps, and the pair's quantities are
+// formed and its key added once per window instead of once per step: two head-on clouds of
+// 1.25 um overlap for 12 steps of 0.1 um/c.
+//   * Clouds are larger than the photons' spacing (a query meets tens of targets per window),
+//     so its neighbours reach nearly the same leaves: the wave descends once, with the hull of
+//     its queries' boxes, 64 pending nodes at a time (lane = node; one load per internal node,
+//     both children tested from it).
+//   * A leaf that passes is tested against the queries' own boxes, four leaves at a time; the
+//     pairs that meet are queued in LDS and evaluated 64 at a time, so that every lane of the
+//     long FP64 pair code works, however unequal the queries are.
+//   * Neighbouring pairs of one bin pair are added up across the wave before the table.
+// Bound by the pair code's FP64 chain and the table's atomics. The exact pass of 2e4 clouds per
+// beam over 400 steps takes 1.8 ms; with one lane per query and window, each with a descent of
+// its own, 2.4 ms (0.8 ms of it descents, and the heaviest waves set the time), and with one
+// descent and one evaluation per step 20.7 ms. Four waves per SIMD (128 VGPRs, some of the
+// pair code's constants spilled) against two unspilled: 9.5 against 9.8 ms for the training
+// rows of that instance; five: 11.0 ms.
+__global__ void __launch_bounds__(64, 4) k_st_traverse(
     const Node *__restrict__ nodes, int32_t n_int, const PBox *__restrict__ root_box,
-    const PBox *__restrict__ qbox, const uint32_t *__restrict__ qorder, int64_t order_len,
-    int64_t nq, int64_t nq_base, const int32_t *__restrict__ inst_root, BeamDev q, BeamDev t,
-    const int32_t *__restrict__ q_bins, const int32_t *__restrict__ t_bins, int64_t n_t_bins,
-    double dt, StCell cell, int geometric, const long long *__restrict__ filter, uint64_t fmask,
+    const PBox *__restrict__ qbox, const uint32_t *__restrict__ qorder, int64_t nq, int64_t groups,
+    const int32_t *__restrict__ inst_root, int64_t n_t, const StRec *__restrict__ qrec,
+    const StRec *__restrict__ trec, int64_t n_t_bins, double dt, int32_t win, int32_t k_begin,
+    int32_t k_last, StCell cell, int mode, const long long *__restrict__ filter, uint64_t fmask,
     long long *keys, double *vals, uint64_t mask, double *__restrict__ slots, DevCounters *c) {
-    const int64_t e = blockIdx.x * (int64_t)BLOCK + threadIdx.x;
-    int32_t node = -1, qi = 0, tag = -1;
+    __shared__ int32_t s_node[kStStack];
+    __shared__ int32_t s_leaf[192];          // queued pairs: target row
+    __shared__ uint8_t s_owner[192];         //               and query lane
+    __shared__ int32_t s_row[kStQueries];
+    const int lane = threadIdx.x, ql = lane & (kStQueries - 1), grp = lane / kStQueries;
+    const int64_t so = blockIdx.x / groups;  // window of the launch
+    const int64_t qi = (blockIdx.x - so * groups) * kStQueries + ql;
+    int32_t root = -1, tag = -1;
     float qb[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    if (e < nq) {
-        if (qorder == nullptr) {
-            qi = (int32_t)e;
-        } else if (order_len == nq) {
-            qi = (int32_t)qorder[e];
-        } else {  // one step's order, repeated for every step of the launch
-            const int64_t s = e / nq_base;
-            qi = (int32_t)(s * nq_base + qorder[e - s * nq_base]);
-        }
-        const float4 *bp = reinterpret_cast<const float4 *>(qbox + qi);
+    if (qi < nq) {
+        const int32_t row = (int32_t)qorder[qi];
+        const float4 *bp = reinterpret_cast<const float4 *>(qbox + so * nq + row);
         const float4 a = bp[0], b = bp[1];
         qb[0] = a.x; qb[1] = a.y; qb[2] = a.z;
         qb[3] = b.x; qb[4] = b.y; qb[5] = b.z;
         tag = __float_as_int(a.w);
-        if (tag >= 0) node = inst_root[tag];
+        if (tag >= 0 && qrec[row].bin >= 0) root = inst_root[tag];
+        if (grp == 0) s_row[ql] = row;
     }
-    const int64_t so = q.m > 1 ? (int64_t)qi / q.n : 0;
-    const int64_t i = (int64_t)qi - so * q.n;
-    const double tk = (double)((int64_t)c->step + so) * dt;
-    const int32_t bq = node != -1 ? q_bins[i] : -1;
-    if (bq < 0) node = -1;
-    long long cur_key = -1;
-    double acc = 0.0, lane_total = 0.0;
+    // the steps of this (aligned) window
+    const int64_t ws = ((int64_t)c->step + so) * win;
+    const int32_t k0 = (int32_t)max((int64_t)k_begin, ws);
+    const int32_t k1 = (int32_t)min((int64_t)k_last, ws + win - 1);
+    const double V = (cell.c[0] * cell.c[1]) * cell.c[2];
+    const double inv_dt = 1.0 / dt, inv_vv = 1.0 / (V * V);
+    double total = 0.0;
     uint32_t visits = 0, n_pairs = 0;
-    if (node <= -2) {  // an instance of one row: its root is that leaf
-        const int64_t el = link_elem(node);
-        const float4 *lp = reinterpret_cast<const float4 *>(root_box + tag);
-        ++visits;
-        if (st_overlap(qb, lp[0], lp[1]))
-            st_leaf(q, i, t, el, so, tk, dt, cell, geometric, bq, t_bins, n_t_bins, filter, fmask,
-                    keys, vals, mask, cur_key, acc, lane_total, n_pairs, c);
-        node = -1;
-    }
-    int32_t stack[kStStack];
-    int32_t depth = 0;
-    const uint32_t max_visits = (uint32_t)n_int + 2u;
-    while (node >= 0) {
-        if (visits > max_visits) {
-            atomicOr(&c->err, kErrSpin);
-            break;
+    int queued = 0;  // uniform over the wave
+    // Evaluates the last `cnt` queued pairs (at most 64).
+    auto evaluate = [&](int cnt) {
+        __syncthreads();
+        const int x = queued - cnt + lane;
+        long long key = -1ll;
+        double sum = 0.0;
+        if (lane < cnt) {
+            const int32_t row = s_row[s_owner[x]];
+            uint32_t n;
+            key = st_pair(qrec[row], row, k0, k1, trec, s_leaf[x], n_t, dt, inv_dt, inv_vv, cell,
+                          mode, n_t_bins, filter, fmask, sum, n);
+            n_pairs += n;
+            total += sum;
         }
-        const float4 *np = reinterpret_cast<const float4 *>(nodes + node);
-        const float4 l0 = np[0], l1 = np[1], r0 = np[2], r1 = np[3];
-        ++visits;
-        const int32_t lc = __float_as_int(l0.w), rc = __float_as_int(r0.w);
-        const bool ovl = st_overlap(qb, l0, l1), ovr = st_overlap(qb, r0, r1);
-        if (ovl && lc < 0)
-            st_leaf(q, i, t, link_elem(lc), so, tk, dt, cell, geometric, bq, t_bins, n_t_bins,
-                    filter, fmask, keys, vals, mask, cur_key, acc, lane_total, n_pairs, c);
-        if (ovr && rc < 0)
-            st_leaf(q, i, t, link_elem(rc), so, tk, dt, cell, geometric, bq, t_bins, n_t_bins,
-                    filter, fmask, keys, vals, mask, cur_key, acc, lane_total, n_pairs, c);
-        const bool gol = ovl && lc >= 0, gor = ovr && rc >= 0;
-        if (gol) {
-            if (gor) {
-                if (depth >= kStStack) {
-                    atomicOr(&c->err, kErrSpin);
-                    break;
-                }
-                stack[depth++] = rc;
+        queued -= cnt;
+        // a run of equal keys is added up into its first lane
+        const long long prev = __shfl_up(key, 1);
+        const bool head = lane == 0 || prev != key;
+        unsigned long long heads = __ballot(head);
+        if (heads != ~0ull) {
+            heads = (heads >> lane) >> 1;
+            const int last = heads ? lane + (int)__ffsll(heads) - 1 : 63;  // of this run
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) {
+                const double v = __shfl_down(sum, off);
+                if (lane + off <= last) sum += v;
             }
-            node = lc;
-        } else if (gor) {
-            node = rc;
-        } else {
-            node = depth > 0 ? stack[--depth] : -1;
         }
+        if (head && key >= 0) table_add(keys, vals, mask, key, sum, &c->err);
+        __syncthreads();
+    };
+    const unsigned long long below = (1ull << lane) - 1ull;
+    auto queue_pair = [&](bool meets, int32_t leaf_row) {
+        const unsigned long long b = __ballot(meets);
+        if (meets) {
+            const int at = queued + (int)__popcll(b & below);
+            s_leaf[at] = leaf_row;
+            s_owner[at] = (uint8_t)ql;
+        }
+        queued += (int)__popcll(b);
+    };
+    // one descent per hierarchy that the queries belong to (one per instance; nearly always
+    // one for the wave)
+    for (unsigned long long todo = __ballot(root != -1); todo != 0ull;) {
+        const int32_t r0 = __shfl(root, (int)__ffsll(todo) - 1);
+        const bool mine = root == r0;
+        todo &= ~__ballot(mine);
+        if (r0 <= -2) {  // an instance of one row: its root is that leaf
+            bool meets = false;
+            if (mine && grp == 0) {
+                const float4 *lp = reinterpret_cast<const float4 *>(root_box + tag);
+                ++visits;
+                meets = st_overlap(qb, lp[0], lp[1]);
+            }
+            // (at most kStQueries of these in all: one per query)
+            queue_pair(meets, (int32_t)(link_elem(r0) - so * n_t));
+            continue;
+        }
+        float hull[6];
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            hull[a] = mine ? qb[a] : INFINITY;
+            hull[3 + a] = mine ? qb[3 + a] : -INFINITY;
+#pragma unroll
+            for (int off = kStQueries / 2; off >= 1; off >>= 1) {
+                hull[a] = fminf(hull[a], __shfl_xor(hull[a], off));
+                hull[3 + a] = fmaxf(hull[3 + a], __shfl_xor(hull[3 + a], off));
+            }
+        }
+        if (lane == 0) s_node[0] = r0;
+        int top = 1;  // uniform over the wave
+        uint32_t seen = 0;
+        while (top > 0) {
+            __syncthreads();
+            // 64 nodes at a time add at most 64 to the stack per level; when it is nearly full,
+            // one at a time adds one per level
+            const int take = top > kStStack - 128 - kStDepth ? 1 : min(top, 64);
+            top -= take;
+            seen += (uint32_t)take;
+            if (seen > (uint32_t)n_int + 2u || top > kStStack - 130) {
+                if (lane == 0) atomicOr(&c->err, kErrSpin);
+                break;
+            }
+            float4 l0{}, l1{}, r0v{}, r1{};
+            int32_t lc = -1, rc = -1;
+            bool ovl = false, ovr = false;
+            if (lane < take) {
+                const float4 *np = reinterpret_cast<const float4 *>(nodes + s_node[top + lane]);
+                l0 = np[0]; l1 = np[1]; r0v = np[2]; r1 = np[3];
+                ++visits;
+                lc = __float_as_int(l0.w);
+                rc = __float_as_int(r0v.w);
+                ovl = st_overlap(hull, l0, l1);
+                ovr = st_overlap(hull, r0v, r1);
+            }
+            __syncthreads();
+#pragma unroll 1
+            for (int side = 0; side < 2; ++side) {
+                const int32_t ch = side ? rc : lc;
+                const bool ov = side ? ovr : ovl;
+                const unsigned long long in = __ballot(ov && ch >= 0);
+                if (ov && ch >= 0) s_node[top + (int)__popcll(in & below)] = ch;
+                top += (int)__popcll(in);
+                // leaves: each group of kStQueries lanes takes one
+                for (unsigned long long lv = __ballot(ov && ch < 0); lv != 0ull;) {
+                    int src = -1;
+#pragma unroll
+                    for (int g = 0; g < 64 / kStQueries; ++g) {
+                        const int at = (int)__ffsll(lv) - 1;  // -1: none left
+                        if (g == grp) src = at;
+                        lv &= lv - 1ull;
+                    }
+                    const int from = src < 0 ? lane : src;
+                    float4 lo, hi;
+                    lo.x = __shfl(side ? r0v.x : l0.x, from);
+                    lo.y = __shfl(side ? r0v.y : l0.y, from);
+                    lo.z = __shfl(side ? r0v.z : l0.z, from);
+                    hi.x = __shfl(side ? r1.x : l1.x, from);
+                    hi.y = __shfl(side ? r1.y : l1.y, from);
+                    hi.z = __shfl(side ? r1.z : l1.z, from);
+                    const int32_t link = __shfl(ch, from);
+                    queue_pair(src >= 0 && mine && st_overlap(qb, lo, hi),
+                               (int32_t)(link_elem(link) - so * n_t));
+                    if (queued >= 64) evaluate(64);
+                }
+            }
+        }
+        __syncthreads();
     }
-    if (cur_key >= 0) table_add(keys, vals, mask, cur_key, acc, &c->err);
+    while (queued > 0) evaluate(min(queued, 64));
     // per-wave sums into spread slots
     unsigned long long v = visits, np_ = n_pairs;
-    double tot = lane_total;
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) {
         v += __shfl_xor(v, off);
         np_ += __shfl_xor(np_, off);
-        tot += __shfl_xor(tot, off);
+        total += __shfl_xor(total, off);
     }
-    if ((threadIdx.x & 63) == 0) {
+    if (lane == 0) {
         const int slot = blockIdx.x & (kCounterSlots - 1);
         if (v) atomicAdd(&c->visits[slot], v);
-        if (np_) atomicAdd(&c->st_pairs, np_);
-        if (tot != 0.0) atomicAdd(&slots[slot], tot);
+        if (np_) atomicAdd(&c->st_pairs[slot], np_);
+        if (total != 0.0) atomicAdd(&slots[slot], total);
     }
 }
 
@@ -559,38 +752,66 @@ __global__ void k_st_records(const double *__restrict__ sums, int64_t n_bins, do
 // log E_a, log E_b, log(1 - cos theta_ab) (theta between the mean directions), log rho_a,
 // log rho_b, log Omega (rho = bin total / cell volume); and the bin-level yield
 // Y0 = rho_a rho_b sigma(s_ab) (1 - cos theta_ab) Omega.
-__global__ void k_st_features(const long long *__restrict__ keys, const double *__restrict__ vals,
-                              int64_t cap, int64_t n_t_bins, const double *__restrict__ q_sums,
-                              const double *__restrict__ t_sums, double vol, float *__restrict__ x,
-                              double *__restrict__ y0, long long *__restrict__ key_out,
-                              int64_t out_cap, unsigned long long *__restrict__ count) {
-    const int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (k >= cap) return;
-    const long long key = keys[k];
-    if (key < 0) return;
-    const double om = vals[k];
-    if (!(om > 0.0)) return;
-    const int64_t a = key / n_t_bins, b = key - a * n_t_bins;
-    const double *sa = q_sums + kStSums * a, *sb = t_sums + kStSums * b;
-    const double Ea = sa[1] / sa[0], Eb = sb[1] / sb[0];
-    const double ua[3] = {sa[2], sa[3], sa[4]}, ub[3] = {sb[2], sb[3], sb[4]};
-    const double na = sqrt((ua[0] * ua[0] + ua[1] * ua[1]) + ua[2] * ua[2]);
-    const double nb = sqrt((ub[0] * ub[0] + ub[1] * ub[1]) + ub[2] * ub[2]);
-    const double cth = ((ua[0] * ub[0] + ua[1] * ub[1]) + ua[2] * ub[2]) / (na * nb);
-    const double qf = fmax(1.0 - cth, 1e-300);
-    const double s = ((Ea * Eb) * qf) / (2.0 * kMe * kMe);
-    const double ra = sa[0] / vol, rb = sb[0] / vol;
-    const unsigned long long r = atomicAdd(count, 1ull);
-    if ((int64_t)r >= out_cap) return;
-    float *f = x + kMlpIn * r;
-    f[0] = (float)log(Ea);
-    f[1] = (float)log(Eb);
-    f[2] = (float)log(qf);
-    f[3] = (float)log(ra);
-    f[4] = (float)log(rb);
-    f[5] = (float)log(om);
-    y0[r] = ((ra * rb) * bw_sigma(s)) * qf * om;
-    key_out[r] = key;
+// Slots are taken kFeatSlots per thread and a workgroup claims its rows with one atomic: with
+// one per row, the counter's address was the whole kernel (3.2 ms per 2^22 slots).
+constexpr int kFeatSlots = 4;
+__global__ void __launch_bounds__(256) k_st_features(
+    const long long *__restrict__ keys, const double *__restrict__ vals, int64_t cap,
+    int64_t n_t_bins, const double *__restrict__ q_sums, const double *__restrict__ t_sums,
+    double vol, float *__restrict__ x, double *__restrict__ y0, long long *__restrict__ key_out,
+    int64_t out_cap, unsigned long long *__restrict__ count) {
+    __shared__ unsigned int s_wave[4];
+    __shared__ unsigned long long s_base;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t k0 = blockIdx.x * (int64_t)(256 * kFeatSlots) + threadIdx.x;
+    long long key[kFeatSlots];
+    double om[kFeatSlots];
+    unsigned int rank[kFeatSlots];
+    unsigned int n = 0;  // rows of this wave so far
+#pragma unroll
+    for (int r = 0; r < kFeatSlots; ++r) {
+        const int64_t k = k0 + 256 * r;
+        key[r] = k < cap ? keys[k] : -1ll;
+        om[r] = key[r] >= 0 ? vals[k] : 0.0;
+        const bool has = om[r] > 0.0;
+        const unsigned long long b = __ballot(has);
+        rank[r] = n + (unsigned int)__popcll(b & ((1ull << lane) - 1ull));
+        if (!has) key[r] = -1ll;
+        n += (unsigned int)__popcll(b);
+    }
+    if (lane == 0) s_wave[wave] = n;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const unsigned int all = (s_wave[0] + s_wave[1]) + (s_wave[2] + s_wave[3]);
+        s_base = all ? atomicAdd(count, (unsigned long long)all) : 0ull;
+    }
+    __syncthreads();
+    unsigned long long base = s_base;
+    for (int w = 0; w < wave; ++w) base += s_wave[w];
+#pragma unroll
+    for (int r = 0; r < kFeatSlots; ++r) {
+        const int64_t row = (int64_t)(base + rank[r]);
+        if (key[r] < 0 || row >= out_cap) continue;
+        const int64_t a = key[r] / n_t_bins, b = key[r] - a * n_t_bins;
+        const double *sa = q_sums + kStSums * a, *sb = t_sums + kStSums * b;
+        const double Ea = sa[1] / sa[0], Eb = sb[1] / sb[0];
+        const double ua[3] = {sa[2], sa[3], sa[4]}, ub[3] = {sb[2], sb[3], sb[4]};
+        const double na = sqrt((ua[0] * ua[0] + ua[1] * ua[1]) + ua[2] * ua[2]);
+        const double nb = sqrt((ub[0] * ub[0] + ub[1] * ub[1]) + ub[2] * ub[2]);
+        const double cth = ((ua[0] * ub[0] + ua[1] * ub[1]) + ua[2] * ub[2]) / (na * nb);
+        const double qf = fmax(1.0 - cth, 1e-300);
+        const double s = ((Ea * Eb) * qf) / (2.0 * kMe * kMe);
+        const double ra = sa[0] / vol, rb = sb[0] / vol;
+        float *f = x + kMlpIn * row;
+        f[0] = (float)log(Ea);
+        f[1] = (float)log(Eb);
+        f[2] = (float)log(qf);
+        f[3] = (float)log(ra);
+        f[4] = (float)log(rb);
+        f[5] = (float)log(om[r]);
+        y0[row] = ((ra * rb) * bw_sigma(s)) * qf * om[r];
+        key_out[row] = key[r];
+    }
 }
 
 // Training targets log((Y + eps Y0) / Y0), Y the exact yield of the row's bin pair (0 when
@@ -758,7 +979,7 @@ void launch_st_features(const long long *keys, const double *vals, int64_t cap, 
                         const double *q_sums, const double *t_sums, double vol, float *x,
                         double *y0, long long *key_out, int64_t out_cap, unsigned long long *count,
                         hipStream_t st) {
-    hipLaunchKernelGGL(k_st_features, dim3(grid_for(cap, 256)), dim3(256), 0, st, keys, vals, cap,
+    hipLaunchKernelGGL(k_st_features, dim3(grid_for(cap, 256 * kFeatSlots)), dim3(256), 0, st, keys, vals, cap,
                        n_t_bins, q_sums, t_sums, vol, x, y0, key_out, out_cap, count);
 }
 
@@ -830,21 +1051,25 @@ void launch_st_clear(long long *keys, double *vals, int64_t cap, double *slots, 
     hipLaunchKernelGGL(k_st_clear, dim3(grid_for(n, 256)), dim3(256), 0, st, keys, vals, cap, slots);
 }
 
+void launch_st_pack(const BeamDev &b, const int32_t *bins, StRec *rec, hipStream_t st) {
+    if (b.n <= 0) return;
+    hipLaunchKernelGGL(k_st_pack, dim3(grid_for(b.n, 256)), dim3(256), 0, st, b, bins, rec);
+}
+
 void launch_st_traverse(const Node *nodes, int64_t n_int64, const PBox *root_box, const PBox *qbox,
-                        const uint32_t *qorder, int64_t order_len, int64_t nq, int64_t nq_base,
-                        const int32_t *inst_root,
-                        const BeamDev &q, const BeamDev &t, const int32_t *q_bins,
-                        const int32_t *t_bins, int64_t n_t_bins, double dt, const StCell &cell,
-                        int geometric, const long long *filter, int64_t filter_cap,
-                        long long *keys, double *vals, int64_t cap, double *slots, DevCounters *c,
-                        hipStream_t st) {
-    if (nq <= 0 || n_int64 < 0) return;
-    const int32_t n_int = (int32_t)n_int64;
-    hipLaunchKernelGGL(k_st_traverse<256>, dim3(grid_for(nq, 256)), dim3(256), 0, st, nodes, n_int,
-                       root_box, qbox, qorder, order_len, nq, nq_base, inst_root, q, t, q_bins,
-                       t_bins, n_t_bins, dt,
-                       cell, geometric, filter, (uint64_t)(filter ? filter_cap - 1 : 0), keys, vals,
-                       (uint64_t)(cap - 1), slots, c);
+                        const uint32_t *qorder, int64_t nq, int32_t m, const int32_t *inst_root,
+                        int64_t n_t, const StRec *qrec, const StRec *trec, int64_t n_t_bins,
+                        double dt, int32_t win, int32_t k_begin, int32_t k_last,
+                        const StCell &cell, int mode, const long long *filter,
+                        int64_t filter_cap, long long *keys, double *vals, int64_t cap,
+                        double *slots, DevCounters *c, hipStream_t st) {
+    if (nq <= 0 || m <= 0 || n_int64 < 0) return;
+    const int64_t groups = (nq + kStQueries - 1) / kStQueries;
+    hipLaunchKernelGGL(k_st_traverse, dim3((unsigned)(groups * m)), dim3(64), 0, st, nodes,
+                       (int32_t)n_int64, root_box, qbox, qorder, nq, groups, inst_root, n_t, qrec,
+                       trec, n_t_bins, dt, win, k_begin, k_last, cell, mode, filter,
+                       (uint64_t)(filter ? filter_cap - 1 : 0), keys, vals, (uint64_t)(cap - 1),
+                       slots, c);
 }
 
 }  // namespace tril

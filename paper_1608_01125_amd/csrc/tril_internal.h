@@ -258,7 +258,6 @@ struct DevCounters {
     unsigned long long cand_total;
     unsigned long long sigma_evals;
     unsigned long long fp64_rechecks;  // candidates the FP32 stage left to FP64
-    unsigned long long st_pairs;       // statistical regime: cloud pair-steps with a yield
     unsigned long long builds;
     unsigned long long collides;
     unsigned long long trav_next[8];   // work-queue cursors of the persistent traversal
@@ -267,6 +266,8 @@ struct DevCounters {
     unsigned long long visits[kCounterSlots];
     unsigned long long queries[kCounterSlots];
     unsigned long long leaf_checks[kCounterSlots];  // window copies: leaf records read
+    unsigned long long st_pairs[kCounterSlots];     // statistical regime: cloud pair-steps
+                                                    // with a yield
 };
 
 // ---------------------------------------------------------------- radix sort
@@ -344,7 +345,7 @@ void launch_beam_stats(const BeamDev &b, StatsPartial *partials, InstStats *stat
 // virtual element index). Morton quantisation bounds come from self_stats; query
 // padding and the threshold prune from t_stats (target instance statistics).
 // Box kind for launch_boxes_keys: the swept segment of a step (on = 0), or the cloud of
-// the statistical regime (on = 1): a box of half-widths h about the position at mid-step.
+// the statistical regime swept over a window (on = 1): the segment widened by h per axis.
 struct CloudBox {
     int on;
     double h[3];
@@ -620,14 +621,25 @@ void launch_swarm(const long long *pkeys, double *pvals, int64_t pcap, const Bea
                   int64_t n_t_bins, const StCell &cell, double T0, double Tw, long long *keys,
                   double *vals, int64_t cap, unsigned long long *total, DevCounters *c,
                   hipStream_t st);
+// Photons as the cloud traversal reads them (one record per caller row).
+struct alignas(16) StRec {
+    double x[3], u[3];  // position at t = 0, direction p / E
+    double E, w;
+    int32_t bin, pad;
+    int64_t pad1;
+};
+void launch_st_pack(const BeamDev &b, const int32_t *bins, StRec *rec, hipStream_t st);
+// Cloud traversal of m windows of win steps each (window s of the launch covers the steps of
+// [k_begin, k_last] in [(c->step + s) win, (c->step + s + 1) win)) by nq query rows in the
+// order qorder; boxes and hierarchy built with the window as the step. mode: 0 yields,
+// 1 overlap integrals, 2 exposures per cloud pair, 3 swept clouds that meet (win 1).
 void launch_st_traverse(const Node *nodes, int64_t n_int, const PBox *root_box, const PBox *qbox,
-                        const uint32_t *qorder, int64_t order_len, int64_t nq, int64_t nq_base,
-                        const int32_t *inst_root,
-                        const BeamDev &q, const BeamDev &t, const int32_t *q_bins,
-                        const int32_t *t_bins, int64_t n_t_bins, double dt, const StCell &cell,
-                        int geometric, const long long *filter, int64_t filter_cap,
-                        long long *keys, double *vals, int64_t cap, double *slots, DevCounters *c,
-                        hipStream_t st);
+                        const uint32_t *qorder, int64_t nq, int32_t m, const int32_t *inst_root,
+                        int64_t n_t, const StRec *qrec, const StRec *trec, int64_t n_t_bins,
+                        double dt, int32_t win, int32_t k_begin, int32_t k_last,
+                        const StCell &cell, int mode, const long long *filter,
+                        int64_t filter_cap, long long *keys, double *vals, int64_t cap,
+                        double *slots, DevCounters *c, hipStream_t st);
 
 // ------------------------------------------------------------ annihilation mode
 // Scratch of annihilate_hits: per raw hit (cap) two sort key/value buffer pairs, rank,
