@@ -2530,17 +2530,14 @@ int tril_mlp_grad(tril_mlp *p, int32_t member, const float *x, const float *y, i
         n > INT32_MAX)
         return TRIL_E_INVAL;
     MlpModel &m = p->m;
-    CHK(mlp_scratch(&m, n));
-    HIPCHK(hipMemsetAsync(m.loss, 0, sizeof(float), m.st));
-    mlp_input(&m, x, nullptr, n);
-    mlp_forward(&m, member, n, m.yhat);
-    mlp_loss(&m, y, nullptr, n);
-    mlp_backward(&m, member, n);
+    CHK(mlp_scratch(&m, n, 1));
+    HIPCHK(hipMemsetAsync(m.loss, 0, (size_t)m.K * sizeof(float), m.st));
+    mlp_step(&m, member, 1, x, y, n, n, false, 0, 0, true, 0.0f);
     HIPCHK(hipGetLastError());
     HIPCHK(hipStreamSynchronize(m.st));
     HIPCHK(hipMemcpy(host_grad, m.g, kMlpParams * sizeof(float), hipMemcpyDeviceToHost));
     float l = 0.f;
-    HIPCHK(hipMemcpy(&l, m.loss, sizeof(float), hipMemcpyDeviceToHost));
+    HIPCHK(hipMemcpy(&l, m.loss + member, sizeof(float), hipMemcpyDeviceToHost));
     *host_loss = (double)l / (double)n;
     return TRIL_OK;
 }
@@ -2550,32 +2547,23 @@ int tril_mlp_train(tril_mlp *p, const float *x, const float *y, int64_t n, int32
     if (!p || !x || !y || n < 1 || n > INT32_MAX || n_steps < 0 || batch < 1 || !(lr > 0.0f))
         return TRIL_E_INVAL;
     MlpModel &m = p->m;
-    CHK(mlp_scratch(&m, batch));
+    const int group = mlp_train_group(&m, batch);
+    CHK(mlp_scratch(&m, batch, group));
     const int32_t tail = std::max(1, n_steps / 10);
-    std::vector<double> acc((size_t)m.K, 0.0);
-    for (int k = 0; k < m.K; ++k) {
-        HIPCHK(hipMemsetAsync(m.loss, 0, sizeof(float), m.st));
-        for (int32_t s = 0; s < n_steps; ++s) {
-            mlp_batch_idx(&m, seed, k, m.adam_t + s, n, batch);
-            mlp_input(&m, x, m.idx, batch);
-            mlp_forward(&m, k, batch, m.yhat);
-            if (s == n_steps - tail) HIPCHK(hipMemsetAsync(m.loss, 0, sizeof(float), m.st));
-            mlp_loss(&m, y, m.idx, batch);
-            mlp_backward(&m, k, batch);
-            mlp_adam(&m, k, lr, m.adam_t + s + 1);
-        }
-        HIPCHK(hipGetLastError());
-        if (host_loss && n_steps > 0) {
-            float l = 0.f;
-            HIPCHK(hipStreamSynchronize(m.st));
-            HIPCHK(hipMemcpy(&l, m.loss, sizeof(float), hipMemcpyDeviceToHost));
-            acc[(size_t)k] = (double)l / ((double)tail * batch);
-        }
-    }
+    HIPCHK(hipMemsetAsync(m.loss, 0, (size_t)m.K * sizeof(float), m.st));
+    for (int k = 0; k < m.K; k += group)
+        for (int32_t s = 0; s < n_steps; ++s)
+            mlp_step(&m, k, std::min(group, m.K - k), x, y, n, batch, true, seed, m.adam_t + s,
+                     s >= n_steps - tail, lr);
+    HIPCHK(hipGetLastError());
     m.adam_t += n_steps;
     HIPCHK(hipStreamSynchronize(m.st));
-    if (host_loss)
-        for (int k = 0; k < m.K; ++k) host_loss[k] = acc[(size_t)k];
+    if (host_loss) {
+        std::vector<float> l((size_t)m.K, 0.0f);
+        HIPCHK(hipMemcpy(l.data(), m.loss, l.size() * sizeof(float), hipMemcpyDeviceToHost));
+        for (int k = 0; k < m.K; ++k)
+            host_loss[k] = n_steps > 0 ? (double)l[(size_t)k] / ((double)tail * batch) : 0.0;
+    }
     return TRIL_OK;
 }
 
@@ -2586,7 +2574,6 @@ int tril_mlp_predict(tril_mlp *p, const float *x, int64_t n, float *mean, float 
     const int64_t chunk = std::min<int64_t>(n, (int64_t)1 << 20);
     float *outs = nullptr;
     CHK(dev_alloc(&outs, (size_t)(m.K * chunk)));
-    mlp_pack_inference(&m);
     for (int64_t a = 0; a < n; a += chunk) {
         const int64_t c = std::min(chunk, n - a);
         for (int k = 0; k < m.K; ++k) mlp_fused_forward(&m, k, x + a * kMlpIn, c, outs + (int64_t)k * c);
@@ -2603,7 +2590,7 @@ int tril_dbg_gemm_bf16(const uint16_t *A, int64_t sam, int64_t sak, const uint16
                        int64_t sbn, int32_t M, int32_t N, int32_t K, float *C, void *stream) {
     if (!A || !B || !C || M < 1 || N < 1 || K < 0) return TRIL_E_INVAL;
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    mlp_gemm(A, sam, sak, B, sbk, sbn, M, N, K, 0, nullptr, nullptr, C, nullptr, nullptr, st);
+    mlp_gemm(A, sam, sak, B, sbk, sbn, M, N, K, C, st);
     HIPCHK(hipGetLastError());
     HIPCHK(hipStreamSynchronize(st));
     return TRIL_OK;

@@ -493,56 +493,53 @@ void launch_pair_eval(int64_t n, const double *in, double *out, hipStream_t st);
 // Surrogate network (mlp.hip): 6 -> 256 -> 256 -> 256 -> 1, K members.
 constexpr int kMlpIn = 6;
 constexpr int kMlpHidden = 256;
-constexpr int kMlpSlices = 16;  // K slices of the weight-gradient products (batch rows)
+constexpr int kMlpSlices = 16;  // slices of the weight-gradient products (batch rows)
 constexpr int64_t kMlpParams = (int64_t)kMlpHidden * kMlpIn + kMlpHidden +
                                2 * ((int64_t)kMlpHidden * kMlpHidden + kMlpHidden) + kMlpHidden + 1;
 
+constexpr int64_t kMlpStride = (kMlpParams + 63) / 64 * 64;  // a member's BF16 weights
 struct MlpModel {
     int K = 0;
     hipStream_t st = nullptr;
     float *w = nullptr;         // FP32 master parameters, K x kMlpParams
-    uint16_t *wb = nullptr;     // BF16 copy
-    uint16_t *wbi = nullptr;    // BF16 copy at an aligned member stride (inference)
+    uint16_t *wb = nullptr;     // BF16 copy, K x kMlpStride (W1 and W4 are read from it)
+    uint16_t *wf = nullptr;     // BF16 W2, W3 and their transposes as matrix-core fragments
     float *g = nullptr;         // gradient of one member
     float *am = nullptr, *av = nullptr;  // Adam moments
     float *norm = nullptr;      // input mean [6], sd [6]
     float mu_y = 0.f, sd_y = 1.f;
-    int64_t rows = 0;           // scratch capacity (rows of a batch)
-    uint16_t *xb = nullptr;
-    float *z1 = nullptr, *z2 = nullptr, *z3 = nullptr;
-    uint16_t *h1 = nullptr, *h2 = nullptr, *h3 = nullptr;
-    float *dz = nullptr, *dz2 = nullptr;
-    uint16_t *dzb = nullptr, *dz2b = nullptr;
-    float *yhat = nullptr, *dy = nullptr;
-    uint16_t *dyb = nullptr;
-    float *loss = nullptr;
-    int32_t *idx = nullptr;
-    float *gpart = nullptr;     // slice partials of the weight gradients (kMlpSlices x H x H)
+    float *loss = nullptr;      // K summed losses
+    // training scratch of the members trained together (mlp_train_group)
+    uint16_t *act = nullptr;    // transposed activations and gradients, kActRows x act_ld each
+    float *part = nullptr;      // slice partials of the weight gradients, kMlpSlices x kMlpParams
+    float *bpart = nullptr;     // 64-row partials of the bias gradients
+    int64_t act_cap = 0, part_cap = 0, bpart_cap = 0;
     int64_t adam_t = 0;
     std::vector<void *> allocs;
     ~MlpModel();
 };
 int mlp_init(MlpModel *m, int K, uint64_t seed, hipStream_t st);
-int mlp_scratch(MlpModel *m, int64_t rows);
-void mlp_input(MlpModel *m, const float *x, const int32_t *idx, int64_t n);
-void mlp_forward(MlpModel *m, int k, int64_t n, float *yhat_out);
-// Inference: refresh the aligned BF16 copy (before the members' forward passes), then one
-// fused forward pass of member k.
-void mlp_pack_inference(MlpModel *m);
+// Members trained together on batches of n rows: all of them within kMlpScratch bytes of
+// scratch, else one after the other in groups (a group of one takes what it needs).
+constexpr int64_t kMlpScratch = (int64_t)1 << 29;
+int mlp_train_group(const MlpModel *m, int64_t n);
+int mlp_scratch(MlpModel *m, int64_t n, int group);
+// One step of members k0 .. k0 + group - 1 on a batch of x [n][6], y [n]: rows drawn by the hash
+// of (seed, member, step, row) and Adam with time step + 1 (hashed), or the first `batch` rows
+// in order and the gradient into m->g, no update (group 1). add_loss: the batch's summed
+// losses are added to m->loss.
+void mlp_step(MlpModel *m, int k0, int group, const float *x, const float *y, int64_t n,
+              int64_t batch, bool hashed, uint64_t seed, int64_t step, bool add_loss, float lr);
+// Inference: one fused forward pass of member k.
 void mlp_fused_forward(MlpModel *m, int k, const float *x, int64_t n, float *out);
-void mlp_loss(MlpModel *m, const float *y, const int32_t *idx, int64_t n);
-void mlp_backward(MlpModel *m, int k, int64_t n);
-void mlp_adam(MlpModel *m, int k, float lr, int64_t t);
 void mlp_reduce(MlpModel *m, const float *out, int64_t n, float *mean, float *sdev);
 void mlp_cast(MlpModel *m);
-void mlp_batch_idx(MlpModel *m, uint64_t seed, int k, int64_t step, int64_t n, int64_t batch);
 // Column sums and sums of squares into out[2 c] (written, fixed-order reduction); part:
 // scratch of 2 c kMomentSlices doubles; c <= 64.
 constexpr int kMomentSlices = 256;
 void mlp_moments(const float *a, int64_t n, int c, double *out, double *part, hipStream_t st);
 void mlp_gemm(const uint16_t *A, int64_t sam, int64_t sak, const uint16_t *B, int64_t sbk,
-              int64_t sbn, int M, int N, int K, int epi, const float *bias, const float *aux,
-              float *out, uint16_t *out_bf, float *out_pre, hipStream_t st);
+              int64_t sbn, int M, int N, int K, float *out, hipStream_t st);
 
 // Statistical regime (st.hip).
 struct StGridDev {
