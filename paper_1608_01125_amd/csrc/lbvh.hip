@@ -243,7 +243,7 @@ __global__ void __launch_bounds__(kStatThreads) k_beam_stats(BeamDev b, StatsPar
         else st_atomic(stats + m, one);
     }
     st_wave(r0);
-    st_wave(r1);
+    if (m_hi != m_lo) st_wave(r1);  // else nothing went there
     const int wave = threadIdx.x >> 6;
     if ((threadIdx.x & 63) == 0) {
         s_red[wave][0] = r0;
@@ -253,7 +253,7 @@ __global__ void __launch_bounds__(kStatThreads) k_beam_stats(BeamDev b, StatsPar
     if (threadIdx.x == 0) {
         for (int w = 1; w < kStatThreads / 64; ++w) {
             st_merge(r0, s_red[w][0]);
-            st_merge(r1, s_red[w][1]);
+            if (m_hi != m_lo) st_merge(r1, s_red[w][1]);
         }
         StatsPartial p0, p1;
         p0.s = r0;
@@ -267,7 +267,8 @@ __global__ void __launch_bounds__(kStatThreads) k_beam_stats(BeamDev b, StatsPar
     }
 }
 
-// One workgroup per instance folds that instance's block partials into its totals.
+// One workgroup per instance folds that instance's block partials into its totals (one
+// instance: the partials are all there is).
 __global__ void __launch_bounds__(256) k_fold_stats(const StatsPartial *__restrict__ partials,
                                                     BeamDev b, InstStats *stats) {
     __shared__ InstStats s_red[4];
@@ -279,7 +280,7 @@ __global__ void __launch_bounds__(256) k_fold_stats(const StatsPartial *__restri
     if (e > a) {
         const int64_t b0 = a / kStatSpan, b1 = (e - 1) / kStatSpan;
         for (int64_t blk = b0 + threadIdx.x; blk <= b1; blk += blockDim.x) {
-            for (int sl = 0; sl < 2; ++sl) {
+            for (int sl = 0; sl < (b.n_inst > 1 ? 2 : 1); ++sl) {
                 const StatsPartial &p = partials[2 * blk + sl];
                 if (p.inst == m) st_merge(r, p.s);
             }
@@ -290,7 +291,8 @@ __global__ void __launch_bounds__(256) k_fold_stats(const StatsPartial *__restri
     __syncthreads();
     if (threadIdx.x == 0) {
         for (int w = 1; w < (int)(blockDim.x / 64); ++w) st_merge(r, s_red[w]);
-        st_atomic(stats + m, r);
+        if (b.n_inst > 1) st_atomic(stats + m, r);
+        else *stats = r;
     }
 }
 
@@ -1402,8 +1404,9 @@ int64_t stats_partials_needed(int64_t n) { return 2 * ((n + kStatSpan - 1) / kSt
 
 void launch_beam_stats(const BeamDev &b, StatsPartial *partials, InstStats *stats, DevCounters *c,
                        hipStream_t st, bool light_like, double *rows) {
-    hipLaunchKernelGGL(k_stats_clear, dim3(grid_for(b.n_inst, 64)), dim3(64), 0, st, stats,
-                       b.n_inst);
+    if (b.n_inst > 1 || b.n <= 0)
+        hipLaunchKernelGGL(k_stats_clear, dim3(grid_for(b.n_inst, 64)), dim3(64), 0, st, stats,
+                           b.n_inst);
     if (b.n <= 0) return;
     hipLaunchKernelGGL(k_beam_stats, dim3(grid_for(b.n, kStatSpan)), dim3(kStatThreads), 0, st, b,
                        partials, stats, c, light_like ? 1 : 0,

@@ -11,6 +11,9 @@
 //      no release fence (an L2 write-back on this chip) is needed,
 //   3. stages keys in digit order in LDS and writes each digit's run to its global
 //      bucket with consecutive lanes on consecutive addresses.
+// Up to kSmallSort keys one workgroup does every pass with its keys in registers
+// (k_sort_small). Up to kMidSort keys the tiles are of 1024 keys instead of 4096: such a pass is
+// one round of tiles whatever their size, and a quarter of the keys per thread shortens it.
 // Published methods: Merrill & Garland, "Single-pass parallel prefix scan with
 // decoupled look-back" (2016); Adinets & Merrill, "Onesweep" (2022).
 #include "tril_internal.h"
@@ -23,6 +26,17 @@ constexpr int kBlock = 256;
 constexpr int kWaves = kBlock / 64;
 constexpr int kItems = 16;
 constexpr int kTile = kBlock * kItems;  // 4096 keys per tile
+constexpr int kItemsMid = 4;
+constexpr int64_t kMidSort = (int64_t)1 << 18;
+// One workgroup is the faster while its passes, about 0.8 us per thousand keys and pass on top of
+// 2 us, stay below a launch of tiles (8 us, one round of them). Three passes: 10 us at 2000
+// keys, 25 at 8000, 32 at 10000 and 47 at 16000, against 51, 61 and 64 with tiles of 4096 as
+// separate launches; a program stepping through 1e4 photons (two sorts of four passes a step)
+// took 178 us per step with tiles, 190 with one workgroup.
+constexpr int kSmallBlock = 1024;
+constexpr int64_t kSmallSort = 8 * kSmallBlock;
+
+int64_t tile_of(int64_t n) { return n <= kMidSort ? kBlock * kItemsMid : kTile; }
 constexpr uint32_t kFlagAgg = 1u << 30;
 constexpr uint32_t kFlagInc = 2u << 30;
 constexpr uint32_t kValMask = (1u << 30) - 1u;
@@ -101,11 +115,120 @@ __global__ void __launch_bounds__(kBlock) k_sort_hist(const K *__restrict__ keys
     }
 }
 
-template <typename K>
+// Every pass of a sort of at most kSmallBlock ITEMS keys in one workgroup, result in place. The
+// keys stay in registers between the passes (wave-major as in k_sort_pass) and change places
+// through one LDS buffer, first the keys, then the values: a sort of a few thousand keys as five
+// or six launches is a chain of their latencies.
+template <typename K, int ITEMS>
+__global__ void __launch_bounds__(kSmallBlock) k_sort_small(K *__restrict__ keys,
+                                                            uint32_t *__restrict__ vals, int n,
+                                                            int per, int passes) {
+    constexpr int kW = kSmallBlock / 64;
+    __shared__ K s_x[kSmallBlock * ITEMS];
+    __shared__ uint32_t s_cnt[kW * 256];
+    __shared__ uint32_t s_tmp[4];
+    uint32_t *s_v = reinterpret_cast<uint32_t *>(s_x);
+    const int tid = threadIdx.x;
+    const uint32_t lane = lane_id(), wave = tid >> 6;
+    const int base = (int)wave * (64 * per) + (int)lane;
+    K key[ITEMS];
+    uint32_t val[ITEMS], pos[ITEMS];
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it) {
+        const int idx = base + it * 64;
+        const bool valid = it < per && idx < n;
+        key[it] = valid ? keys[idx] : (K)0;
+        val[it] = valid ? vals[idx] : 0u;
+    }
+    for (int p = 0; p < passes; ++p) {
+        for (int i = tid; i < kW * 256; i += kSmallBlock) s_cnt[i] = 0u;
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < ITEMS; ++it) {
+            const bool valid = it < per && base + it * 64 < n;
+            if (it < per) {  // uniform
+                const uint32_t d = (uint32_t)((key[it] >> (8 * p)) & 255u);
+                unsigned long long peers = __ballot(valid);
+    #pragma unroll
+                for (int b = 0; b < 8; ++b) {
+                    const bool bit = (d >> b) & 1u;
+                    const unsigned long long bb = __ballot(bit);
+                    peers &= bit ? bb : ~bb;
+                }
+                const uint32_t rank = count_below(peers);
+                const int leader = peers ? (__ffsll((long long)peers) - 1) : 0;
+                uint32_t old = 0u;
+                if (valid && lane == (uint32_t)leader) {
+                    old = s_cnt[wave * 256 + d];
+                    s_cnt[wave * 256 + d] = old + (uint32_t)__popcll(peers);
+                }
+                pos[it] = __shfl(old, leader) + rank;
+            }
+        }
+        __syncthreads();
+        // per digit: exclusive prefix over the waves on top of the prefix over the digits
+        uint32_t cnt[kW], all = 0;
+        if (tid < 256) {
+#pragma unroll
+            for (int w = 0; w < kW; ++w) {
+                cnt[w] = s_cnt[w * 256 + tid];
+                all += cnt[w];
+            }
+        }
+        uint32_t x = all;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t y = __shfl_up(x, off);
+            if (lane >= (uint32_t)off) x += y;
+        }
+        if (tid < 256 && lane == 63) s_tmp[wave] = x;
+        __syncthreads();
+        if (tid < 256) {
+            uint32_t run = x - all;
+            for (uint32_t w = 0; w < wave; ++w) run += s_tmp[w];
+#pragma unroll
+            for (int w = 0; w < kW; ++w) {
+                s_cnt[w * 256 + tid] = run;
+                run += cnt[w];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < ITEMS; ++it)
+            if (it < per && base + it * 64 < n) {
+                pos[it] += s_cnt[wave * 256 + (uint32_t)((key[it] >> (8 * p)) & 255u)];
+                s_x[pos[it]] = key[it];
+            }
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < ITEMS; ++it)
+            if (it < per && base + it * 64 < n) key[it] = s_x[base + it * 64];
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < ITEMS; ++it)
+            if (it < per && base + it * 64 < n) s_v[pos[it]] = val[it];
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < ITEMS; ++it)
+            if (it < per && base + it * 64 < n) val[it] = s_v[base + it * 64];
+        __syncthreads();
+    }
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it) {
+        const int idx = base + it * 64;
+        if (it < per && idx < n) {
+            keys[idx] = key[it];
+            vals[idx] = val[it];
+        }
+    }
+}
+
+template <typename K, int kItems>
 __global__ void __launch_bounds__(kBlock) k_sort_pass(
     const K *__restrict__ kin, const uint32_t *__restrict__ vin, K *__restrict__ kout,
     uint32_t *__restrict__ vout, int64_t n, int shift, const uint32_t *__restrict__ hist,
     uint32_t *status, uint32_t *tile_ctr, unsigned int *err) {
+    constexpr int kTile = kBlock * kItems;
     __shared__ uint32_t s_tile;
     __shared__ uint32_t s_wcnt[kWaves * 256];
     __shared__ uint32_t s_tprefix[256];
@@ -248,7 +371,16 @@ bool sort_impl(K *keys, uint32_t *vals, K *keys_alt, uint32_t *vals_alt, int64_t
                const SortScratch &s, unsigned int *err, hipStream_t st) {
     if (n <= 1 || key_bits <= 0) return false;
     const int passes = (key_bits + 7) / 8;
-    const int64_t tiles = (n + kTile - 1) / kTile;
+    if (n <= kSmallSort) {
+        const dim3 one(1), block(kSmallBlock);
+        const int per = (int)((n + kSmallBlock - 1) / kSmallBlock);  // keys of a thread
+        if (per <= 4)
+            hipLaunchKernelGGL((k_sort_small<K, 4>), one, block, 0, st, keys, vals, (int)n, per, passes);
+        else
+            hipLaunchKernelGGL((k_sort_small<K, 8>), one, block, 0, st, keys, vals, (int)n, per, passes);
+        return false;
+    }
+    const int64_t tile = tile_of(n), tiles = (n + tile - 1) / tile;
     const size_t words = (size_t)passes * (size_t)tiles * 256;
     {
         int grid = (int)std::min<size_t>((words + 255) / 256, 2048);
@@ -257,15 +389,20 @@ bool sort_impl(K *keys, uint32_t *vals, K *keys_alt, uint32_t *vals_alt, int64_t
                            passes, words);
     }
     {
-        int grid = (int)std::min<int64_t>((n + kBlock * 16 - 1) / (kBlock * 16), 1024);
+        int grid = (int)std::min<int64_t>((n + tile - 1) / tile, 1024);
         hipLaunchKernelGGL(k_sort_hist<K>, dim3(grid), dim3(kBlock), 0, st, keys, n, passes, s.hist);
     }
     K *ki = keys, *ko = keys_alt;
     uint32_t *vi = vals, *vo = vals_alt;
     for (int p = 0; p < passes; ++p) {
-        hipLaunchKernelGGL(k_sort_pass<K>, dim3((unsigned)tiles), dim3(kBlock), 0, st, ki, vi, ko,
-                           vo, n, 8 * p, s.hist + 256 * p, s.status + (size_t)p * tiles * 256,
-                           s.tile_ctr + p, err);
+        const dim3 grid((unsigned)tiles), block(kBlock);
+        uint32_t *hist = s.hist + 256 * p, *status = s.status + (size_t)p * tiles * 256;
+        if (tile == kTile)
+            hipLaunchKernelGGL((k_sort_pass<K, kItems>), grid, block, 0, st, ki, vi, ko, vo, n, 8 * p,
+                               hist, status, s.tile_ctr + p, err);
+        else
+            hipLaunchKernelGGL((k_sort_pass<K, kItemsMid>), grid, block, 0, st, ki, vi, ko, vo, n,
+                               8 * p, hist, status, s.tile_ctr + p, err);
         std::swap(ki, ko);
         std::swap(vi, vo);
     }
@@ -274,10 +411,10 @@ bool sort_impl(K *keys, uint32_t *vals, K *keys_alt, uint32_t *vals_alt, int64_t
 
 }  // namespace
 
-int sort_tile_size() { return kTile; }
-
+// Room for a sort of any number of keys up to n.
 size_t sort_status_words(int64_t n, int passes) {
-    const int64_t tiles = (n + kTile - 1) / kTile;
+    const int64_t mid = std::min(n, kMidSort), t = kBlock * kItemsMid;
+    const int64_t tiles = std::max((n + kTile - 1) / kTile, (mid + t - 1) / t);
     return (size_t)passes * (size_t)(tiles > 0 ? tiles : 1) * 256;
 }
 

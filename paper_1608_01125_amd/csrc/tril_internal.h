@@ -278,7 +278,6 @@ struct SortScratch {
     int64_t cap_n = 0;
     int cap_passes = 0;
 };
-int sort_tile_size();
 size_t sort_status_words(int64_t n, int passes);
 // Stable LSD sort of (key, value) on the low key_bits bits. keys/vals hold the input;
 // the result ends in keys/vals or keys_alt/vals_alt; returns true if in *_alt.
