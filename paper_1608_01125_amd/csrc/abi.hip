@@ -78,9 +78,10 @@ constexpr int64_t kBatchStepsMin = 32;
 // steps per window of the cloud traversal: shorter windows meet a pair again and again (a
 // pair's clouds overlap for 12 to 44 steps in the statistical workloads), longer ones reach
 // pairs that never overlap and leave fewer waves. Training rows of 2e4 clouds per beam and the
-// audit of 2e5: 17.4 and 43.8 ms at 4 steps, 13.0 and 32.4 at 8, 11.0 and 26.8 at 16, 11.3
-// and 27.9 at 32, 12.6 and 29.3 at 64.
-constexpr int64_t kStWin = 16;
+// audit of 2e5, 16 queries per wave: 17.4 and 43.8 ms at 4 steps, 13.0 and 32.4 at 8, 11.0 and
+// 26.8 at 16, 11.3 and 27.9 at 32, 12.6 and 29.3 at 64; with 8 queries per wave, as now, 8.93 and
+// 22.1 at 16, 8.69 and 21.7 at 32.
+constexpr int64_t kStWin = 32;
 // with window copies (the plain regime) a launch's tree buffers hold a copy per window, not
 // per step, and its query buffers one record per row: every beam takes up to kBatchBudgetMax
 // virtual elements per launch (the whole 400-step run of two 1e6-photon beams in one launch,
@@ -128,6 +129,13 @@ struct tril_ctx {
     double box_dt = 0.0;            // time one box covers: dt, or a window of the statistical
     int32_t box_steps = 0;          // regime; the steps its launch covers (0: one per box)
     double *st_slots = nullptr;     // statistical regime: per-wave yield sums (kCounterSlots)
+    double *h_st = nullptr;         // pinned host copy of the slots and one word
+    unsigned long long *st_count = nullptr;
+    // feature rows: sort buffers and overlap integrals (fs_cap rows)
+    unsigned long long *fs_ka = nullptr, *fs_kb = nullptr;
+    uint32_t *fs_va = nullptr, *fs_vb = nullptr;
+    double *fs_om = nullptr;
+    int64_t fs_cap = 0;
     StRec *st_qrec = nullptr, *st_trec = nullptr;  // the cloud traversal's photon records
     int64_t st_qrec_cap = 0, st_trec_cap = 0;
     // surrogate path scratch: bin clouds, bin-pair overlap table, features, exact fallback
@@ -1678,16 +1686,43 @@ int st_run(tril_ctx *c, const tril_beam *t, const int32_t *t_bins, int64_t n_t_b
     return TRIL_OK;
 }
 
+// Pinned host memory of the statistical passes: the slots and one word.
+int ensure_st_host(tril_ctx *c) {
+    if (!c->h_st)
+        HIPCHK(hipHostMalloc(reinterpret_cast<void **>(&c->h_st), (kCounterSlots + 1) * sizeof(double),
+                             hipHostMallocDefault));
+    return TRIL_OK;
+}
+
+// Device counter of the row compactions, and its value (synchronises).
+int ensure_st_count(tril_ctx *c) {
+    if (!c->st_count) CHK(dev_alloc(&c->st_count, 1));
+    return ensure_st_host(c);
+}
+
+int read_st_count(tril_ctx *c, int64_t *n) {
+    HIPCHK(hipMemcpyAsync(c->h_st + kCounterSlots, c->st_count, sizeof(unsigned long long),
+                          hipMemcpyDeviceToHost, c->st));
+    HIPCHK(hipStreamSynchronize(c->st));
+    unsigned long long h;
+    std::memcpy(&h, c->h_st + kCounterSlots, sizeof(h));
+    *n = (int64_t)h;
+    return TRIL_OK;
+}
+
 // Sum of the per-wave slots and the device error flags after a pass (synchronises).
 int st_finish(tril_ctx *c, double *total) {
+    CHK(ensure_st_host(c));
+    HIPCHK(hipMemcpyAsync(c->h_st, c->st_slots, kCounterSlots * sizeof(double), hipMemcpyDeviceToHost,
+                          c->st));
+    HIPCHK(hipMemcpyAsync(c->h_st + kCounterSlots, &c->d_cnt->err, sizeof(unsigned int),
+                          hipMemcpyDeviceToHost, c->st));
     HIPCHK(hipStreamSynchronize(c->st));
-    double slots[kCounterSlots];
-    HIPCHK(hipMemcpy(slots, c->st_slots, sizeof(slots), hipMemcpyDeviceToHost));
     double tot = 0.0;
-    for (double v : slots) tot += v;
+    for (int k = 0; k < kCounterSlots; ++k) tot += c->h_st[k];
     if (total) *total = tot;
-    unsigned int err = 0;
-    HIPCHK(hipMemcpy(&err, &c->d_cnt->err, sizeof(err), hipMemcpyDeviceToHost));
+    unsigned int err;
+    std::memcpy(&err, c->h_st + kCounterSlots, sizeof(err));
     if (err & kErrData) return TRIL_E_DATA;
     if (err & kErrSpin) return TRIL_E_INTERNAL;
     if (err & kErrTableFull) return TRIL_E_OVERFLOW;
@@ -1729,32 +1764,24 @@ int check_grid(const tril_st_grid *g) {
 // 8 x cap doubles), their bins in rec_bin; returns the record count in *n.
 int st_records(tril_ctx *c, const double *sums, const tril_st_grid *g, WorkBeam &w,
                int32_t *&rec_bin, int64_t &rec_cap, int64_t *n) {
-    unsigned long long *cnt = nullptr;
-    CHK(dev_alloc(&cnt, 1));
-    int rc = TRIL_OK;
+    CHK(ensure_st_count(c));
     for (int pass = 0; pass < 2; ++pass) {
-        if (hipMemsetAsync(cnt, 0, sizeof(*cnt), c->st) != hipSuccess) {
-            rc = TRIL_E_HIP;
-            break;
-        }
-        launch_st_records(sums, grid_bins(g), g->t_bin, w.soa, w.cap, rec_bin, cnt, c->st);
-        unsigned long long h = 0;
-        if (hipMemcpy(&h, cnt, sizeof(h), hipMemcpyDeviceToHost) != hipSuccess) {
-            rc = TRIL_E_HIP;
-            break;
-        }
-        *n = (int64_t)h;
-        if ((int64_t)h <= w.cap) break;
+        HIPCHK(hipMemsetAsync(c->st_count, 0, sizeof(unsigned long long), c->st));
+        launch_st_records(sums, grid_bins(g), g->t_bin, w.soa, w.cap, rec_bin, c->st_count, c->st);
+        HIPCHK(hipGetLastError());
+        int64_t h = 0;
+        CHK(read_st_count(c, &h));
+        *n = h;
+        if (h <= w.cap) break;
         free_work(w);
         dev_free(rec_bin);
-        if ((rc = dev_alloc(&w.soa, (size_t)(8 * h))) != TRIL_OK) break;
-        if ((rc = dev_alloc(&w.perm, 1)) != TRIL_OK) break;
-        if ((rc = dev_alloc(&rec_bin, (size_t)h)) != TRIL_OK) break;
-        w.cap = (int64_t)h;
-        rec_cap = (int64_t)h;
+        CHK(dev_alloc(&w.soa, (size_t)(8 * h)));
+        CHK(dev_alloc(&w.perm, 1));
+        CHK(dev_alloc(&rec_bin, (size_t)h));
+        w.cap = h;
+        rec_cap = h;
     }
-    dev_free(cnt);
-    return rc;
+    return TRIL_OK;
 }
 
 tril_beam soa_beam(const double *soa, int64_t cap, int64_t n) {
@@ -1779,11 +1806,12 @@ int sur_features(tril_ctx *c, const double *q_sums, const tril_st_grid *gq, cons
 
 // Sum of the per-wave slots (synchronises the stream).
 int slot_sum(tril_ctx *c, double *out) {
+    CHK(ensure_st_host(c));
+    HIPCHK(hipMemcpyAsync(c->h_st, c->st_slots, kCounterSlots * sizeof(double), hipMemcpyDeviceToHost,
+                          c->st));
     HIPCHK(hipStreamSynchronize(c->st));
-    double sl[kCounterSlots];
-    HIPCHK(hipMemcpy(sl, c->st_slots, sizeof(sl), hipMemcpyDeviceToHost));
     double t = 0.0;
-    for (double v : sl) t += v;
+    for (int k = 0; k < kCounterSlots; ++k) t += c->h_st[k];
     *out = t;
     return TRIL_OK;
 }
@@ -2117,55 +2145,42 @@ int tril_st_features(tril_ctx *c, const double *q_sums, const tril_st_grid *gq,
         if (attempt >= 3) return TRIL_E_NOMEM;  // the pair table did not fit the scratch it may take
         tcap = c->sg_cap * 4;
     }
-    // one feature row per occupied slot
-    unsigned long long *cnt = nullptr;
-    CHK(dev_alloc(&cnt, 1));
-    hipError_t e = hipMemsetAsync(cnt, 0, sizeof(*cnt), c->st);
-    const double vol = (cq[0] * cq[1]) * cq[2];
-    launch_st_features(c->sg_key, c->sg_val, c->sg_cap, grid_bins(gt), q_sums, t_sums, vol, x, y0,
-                       reinterpret_cast<long long *>(key), cap, cnt, c->st);
-    unsigned long long h = 0;
-    if (e == hipSuccess) e = hipGetLastError();
-    if (e == hipSuccess) e = hipMemcpy(&h, cnt, sizeof(h), hipMemcpyDeviceToHost);
-    dev_free(cnt);
-    if (e != hipSuccess) return hip_fail(e);
-    *n = (int64_t)h;
-    if ((int64_t)h > cap) return TRIL_E_OVERFLOW;
-    // rows in ascending key order: threads claimed their slots in no fixed order, and the
-    // rows feed training, whose minibatches index them
-    const int64_t nr = (int64_t)h;
-    if (nr < 2) return TRIL_OK;
-    if (nr >= ((int64_t)1 << 32)) return TRIL_E_INVAL;
+    // one feature row per occupied slot, in ascending key order (the rows feed training, whose
+    // minibatches index them); the sort's buffers stay with the context
+    CHK(ensure_st_count(c));
+    int64_t nr = 0;
+    for (int attempt = 0;; ++attempt) {
+        HIPCHK(hipMemsetAsync(c->st_count, 0, sizeof(unsigned long long), c->st));
+        launch_st_compact(c->sg_key, c->sg_val, c->sg_cap, c->fs_ka, c->fs_va, c->fs_om, c->fs_cap,
+                          c->st_count, c->st);
+        HIPCHK(hipGetLastError());
+        CHK(read_st_count(c, &nr));
+        *n = nr;
+        if (nr > cap) return TRIL_E_OVERFLOW;
+        if (nr >= ((int64_t)1 << 32)) return TRIL_E_INVAL;
+        if (nr <= c->fs_cap) break;
+        if (attempt > 0) return TRIL_E_INTERNAL;
+        dev_free(c->fs_ka); dev_free(c->fs_kb); dev_free(c->fs_va); dev_free(c->fs_vb);
+        dev_free(c->fs_om);
+        c->fs_cap = 0;
+        CHK(dev_alloc(&c->fs_ka, (size_t)nr)); CHK(dev_alloc(&c->fs_kb, (size_t)nr));
+        CHK(dev_alloc(&c->fs_va, (size_t)nr)); CHK(dev_alloc(&c->fs_vb, (size_t)nr));
+        CHK(dev_alloc(&c->fs_om, (size_t)nr));
+        c->fs_cap = nr;
+    }
+    if (nr == 0) return TRIL_OK;
     const uint64_t max_key = (uint64_t)grid_bins(gq) * (uint64_t)grid_bins(gt) - 1;
     const int key_bits = std::max(1, bits_for(max_key));
     CHK(ensure_sort_scratch(c, nr));
-    unsigned long long *ka = nullptr, *kb = nullptr;
-    uint32_t *va = nullptr, *vb = nullptr;
-    float *xt = nullptr;
-    double *yt = nullptr;
-    long long *kt = nullptr;
-    int rc = TRIL_OK;
-    if ((rc = dev_alloc(&ka, (size_t)nr)) == TRIL_OK && (rc = dev_alloc(&kb, (size_t)nr)) == TRIL_OK &&
-        (rc = dev_alloc(&va, (size_t)nr)) == TRIL_OK && (rc = dev_alloc(&vb, (size_t)nr)) == TRIL_OK &&
-        (rc = dev_alloc(&xt, (size_t)(kMlpIn * nr))) == TRIL_OK &&
-        (rc = dev_alloc(&yt, (size_t)nr)) == TRIL_OK && (rc = dev_alloc(&kt, (size_t)nr)) == TRIL_OK) {
-        long long *key_ll = reinterpret_cast<long long *>(key);
-        launch_st_keys_iota(key_ll, nr, ka, va, c->st);
-        const bool alt = radix_sort_u64(ka, va, kb, vb, nr, key_bits, c->ss, &c->d_cnt->err, c->st);
-        launch_st_permute_rows(x, y0, key_ll, alt ? vb : va, nr, xt, yt, kt, c->st);
-        e = hipGetLastError();
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(x, xt, (size_t)(kMlpIn * nr) * sizeof(float), hipMemcpyDeviceToDevice, c->st);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(y0, yt, (size_t)nr * sizeof(double), hipMemcpyDeviceToDevice, c->st);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(key_ll, kt, (size_t)nr * sizeof(long long), hipMemcpyDeviceToDevice, c->st);
-        if (e == hipSuccess) e = hipStreamSynchronize(c->st);
-        if (e != hipSuccess) rc = hip_fail(e);
-    }
-    dev_free(ka); dev_free(kb); dev_free(va); dev_free(vb);
-    dev_free(xt); dev_free(yt); dev_free(kt);
-    return rc;
+    const bool alt = radix_sort_u64(c->fs_ka, c->fs_va, c->fs_kb, c->fs_vb, nr, key_bits, c->ss,
+                                    &c->d_cnt->err, c->st);
+    const double vol = (cq[0] * cq[1]) * cq[2];
+    launch_st_features(alt ? c->fs_kb : c->fs_ka, alt ? c->fs_vb : c->fs_va, c->fs_om, nr,
+                       grid_bins(gt), q_sums, t_sums, vol, x, y0, reinterpret_cast<long long *>(key),
+                       c->st);
+    HIPCHK(hipGetLastError());
+    HIPCHK(hipStreamSynchronize(c->st));
+    return TRIL_OK;
 }
 
 int tril_st_targets(const int64_t *key, const double *y0, int64_t n, const tril_st_table *exact,
@@ -2791,6 +2806,9 @@ void tril_destroy(tril_ctx *c) {
         free_work(c->wq[p]);
     }
     dev_free(c->st_slots); dev_free(c->st_qrec); dev_free(c->st_trec);
+    dev_free(c->st_count); dev_free(c->fs_ka); dev_free(c->fs_kb); dev_free(c->fs_va);
+    dev_free(c->fs_vb); dev_free(c->fs_om);
+    if (c->h_st) (void)hipHostFree(c->h_st);
     free_work(c->sr_q); free_work(c->sr_t);
     dev_free(c->sr_q_bin); dev_free(c->sr_t_bin);
     dev_free(c->sg_key); dev_free(c->sg_val);

@@ -41,18 +41,29 @@ __global__ void k_au_control(const long long *__restrict__ key, const double *__
                              double *__restrict__ pa, double *__restrict__ qb,
                              double *__restrict__ slots) {
     const int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    const int lane = threadIdx.x & 63;
     double c = 0.0;
+    int32_t a = -1;
     if (r < n) {
         if (mode == 0) c = scale * fmax(y0[r] * (exp((double)mean[r]) - eps), 0.0);
         else if (mode == 1) c = y0[r];
         ctl[r] = c;
-        if (c > 0.0) {
-            const long long k = key[r];
-            const int64_t a = k / n_t_bins;
-            atomicAdd(pa + a, c);
-            atomicAdd(qb + (k - a * n_t_bins), c);
-        }
+        const long long k = key[r];
+        a = (int32_t)(k / n_t_bins);
+        if (c > 0.0) atomicAdd(qb + (k - a * n_t_bins), c);
     }
+    // rows come in ascending key order: a wave's rows of one query cell are added up first
+    const int32_t prev = __shfl_up(a, 1);
+    const bool head = lane == 0 || prev != a;
+    const unsigned long long heads = (__ballot(head) >> lane) >> 1;
+    const int last = heads ? lane + (int)__ffsll(heads) - 1 : 63;
+    double s = c > 0.0 ? c : 0.0;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const double v = __shfl_down(s, off);
+        if (lane + off <= last) s += v;
+    }
+    if (head && a >= 0 && s > 0.0) atomicAdd(pa + a, s);
     block_add(c, slots);
 }
 

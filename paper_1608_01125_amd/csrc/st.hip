@@ -294,7 +294,7 @@ __device__ __forceinline__ bool st_overlap(const float q[6], float4 lo, float4 h
            (q[5] >= lo.z);
 }
 
-constexpr int kStQueries = 16;  // query photons of one wave
+constexpr int kStQueries = 8;   // query photons of one wave
 constexpr int kStStack = 1024;  // pending nodes of a wave
 constexpr int kStDepth = 128;   // deeper than any radix tree over (key, index) pairs
 
@@ -307,16 +307,18 @@ constexpr int kStDepth = 128;   // deeper than any radix tree over (key, index) 
 //     so its neighbours reach nearly the same leaves: the wave descends once, with the hull of
 //     its queries' boxes, 64 pending nodes at a time (lane = node; one load per internal node,
 //     both children tested from it).
-//   * A leaf that passes is tested against the queries' own boxes, four leaves at a time; the
+//   * A leaf that passes is tested against the queries' own boxes, eight leaves at a time; the
 //     pairs that meet are queued in LDS and evaluated 64 at a time, so that every lane of the
 //     long FP64 pair code works, however unequal the queries are.
 //   * Neighbouring pairs of one bin pair are added up across the wave before the table.
-// Bound by the pair code's FP64 chain and the table's atomics. The exact pass of 2e4 clouds per
-// beam over 400 steps takes 1.8 ms; with one lane per query and window, each with a descent of
-// its own, 2.4 ms (0.8 ms of it descents, and the heaviest waves set the time), and with one
-// descent and one evaluation per step 20.7 ms. Four waves per SIMD (128 VGPRs, some of the
-// pair code's constants spilled) against two unspilled: 9.5 against 9.8 ms for the training
-// rows of that instance; five: 11.0 ms.
+// Bound by the pair code's FP64 chain and the table's atomics, and by the heaviest waves: the
+// queries of a wave are few so that their hull stays tight and no wave holds too many of the
+// dense core (training rows of 2e4 clouds per beam: 10.7 ms with 32 queries per wave, 9.5 with
+// 16, 8.9 with 8 or 4, at windows of 16 steps). The exact pass of that instance took 20.7 ms with
+// a descent and an evaluation per step, 2.4 ms with one lane per query and window of 16 steps
+// (each with a descent of its own), 1.8 ms with 16 queries per wave. Four waves per SIMD (128
+// VGPRs, some of the pair code's constants spilled) against two unspilled: 9.5 against 9.8 ms
+// for the rows; five: 11.0 ms.
 __global__ void __launch_bounds__(64, 4) k_st_traverse(
     const Node *__restrict__ nodes, int32_t n_int, const PBox *__restrict__ root_box,
     const PBox *__restrict__ qbox, const uint32_t *__restrict__ qorder, int64_t nq, int64_t groups,
@@ -850,30 +852,29 @@ __global__ void k_st_records(const double *__restrict__ sums, int64_t n_bins, do
     rec_bin[r] = (int32_t)b;
 }
 
-// Features of every occupied table slot (bin pair a, b with overlap integral Omega):
-// log E_a, log E_b, log(1 - cos theta_ab) (theta between the mean directions), log rho_a,
-// log rho_b, log Omega (rho = bin total / cell volume); and the bin-level yield
-// Y0 = rho_a rho_b sigma(s_ab) (1 - cos theta_ab) Omega.
-// Slots are taken kFeatSlots per thread and a workgroup claims its rows with one atomic: with
-// one per row, the counter's address was the whole kernel (3.2 ms per 2^22 slots).
-constexpr int kFeatSlots = 4;
-__global__ void __launch_bounds__(256) k_st_features(
-    const long long *__restrict__ keys, const double *__restrict__ vals, int64_t cap,
-    int64_t n_t_bins, const double *__restrict__ q_sums, const double *__restrict__ t_sums,
-    double vol, float *__restrict__ x, double *__restrict__ y0, long long *__restrict__ key_out,
-    int64_t out_cap, unsigned long long *__restrict__ count) {
+// Occupied slots of the overlap table, in no order: key, overlap integral and row number (the
+// value the rows are sorted with). Slots are taken kCompactSlots per thread and a workgroup
+// claims its rows with one atomic: with one per row, the counter's address was the whole
+// kernel (3.2 ms per 2^22 slots). Rows beyond cap are counted, not written.
+constexpr int kCompactSlots = 4;
+__global__ void __launch_bounds__(256) k_st_compact(const long long *__restrict__ keys,
+                                                    const double *__restrict__ vals, int64_t n_slots,
+                                                    unsigned long long *__restrict__ key_out,
+                                                    uint32_t *__restrict__ row_out,
+                                                    double *__restrict__ om_out, int64_t cap,
+                                                    unsigned long long *__restrict__ count) {
     __shared__ unsigned int s_wave[4];
     __shared__ unsigned long long s_base;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t k0 = blockIdx.x * (int64_t)(256 * kFeatSlots) + threadIdx.x;
-    long long key[kFeatSlots];
-    double om[kFeatSlots];
-    unsigned int rank[kFeatSlots];
+    const int64_t k0 = blockIdx.x * (int64_t)(256 * kCompactSlots) + threadIdx.x;
+    long long key[kCompactSlots];
+    double om[kCompactSlots];
+    unsigned int rank[kCompactSlots];
     unsigned int n = 0;  // rows of this wave so far
 #pragma unroll
-    for (int r = 0; r < kFeatSlots; ++r) {
+    for (int r = 0; r < kCompactSlots; ++r) {
         const int64_t k = k0 + 256 * r;
-        key[r] = k < cap ? keys[k] : -1ll;
+        key[r] = k < n_slots ? keys[k] : -1ll;
         om[r] = key[r] >= 0 ? vals[k] : 0.0;
         const bool has = om[r] > 0.0;
         const unsigned long long b = __ballot(has);
@@ -891,29 +892,49 @@ __global__ void __launch_bounds__(256) k_st_features(
     unsigned long long base = s_base;
     for (int w = 0; w < wave; ++w) base += s_wave[w];
 #pragma unroll
-    for (int r = 0; r < kFeatSlots; ++r) {
+    for (int r = 0; r < kCompactSlots; ++r) {
         const int64_t row = (int64_t)(base + rank[r]);
-        if (key[r] < 0 || row >= out_cap) continue;
-        const int64_t a = key[r] / n_t_bins, b = key[r] - a * n_t_bins;
-        const double *sa = q_sums + kStSums * a, *sb = t_sums + kStSums * b;
-        const double Ea = sa[1] / sa[0], Eb = sb[1] / sb[0];
-        const double ua[3] = {sa[2], sa[3], sa[4]}, ub[3] = {sb[2], sb[3], sb[4]};
-        const double na = sqrt((ua[0] * ua[0] + ua[1] * ua[1]) + ua[2] * ua[2]);
-        const double nb = sqrt((ub[0] * ub[0] + ub[1] * ub[1]) + ub[2] * ub[2]);
-        const double cth = ((ua[0] * ub[0] + ua[1] * ub[1]) + ua[2] * ub[2]) / (na * nb);
-        const double qf = fmax(1.0 - cth, 1e-300);
-        const double s = ((Ea * Eb) * qf) / (2.0 * kMe * kMe);
-        const double ra = sa[0] / vol, rb = sb[0] / vol;
-        float *f = x + kMlpIn * row;
-        f[0] = (float)log(Ea);
-        f[1] = (float)log(Eb);
-        f[2] = (float)log(qf);
-        f[3] = (float)log(ra);
-        f[4] = (float)log(rb);
-        f[5] = (float)log(om[r]);
-        y0[row] = ((ra * rb) * bw_sigma(s)) * qf * om[r];
-        key_out[row] = key[r];
+        if (key[r] < 0 || row >= cap) continue;
+        key_out[row] = (unsigned long long)key[r];
+        row_out[row] = (uint32_t)row;
+        om_out[row] = om[r];
     }
+}
+
+// Feature rows in ascending key order (key, the compacted rows' numbers in that order and their
+// overlap integrals Omega; bin pair a, b): log E_a, log E_b, log(1 - cos theta_ab) (theta between
+// the mean directions), log rho_a, log rho_b, log Omega (rho = bin total / cell volume); and the
+// bin-level yield Y0 = rho_a rho_b sigma(s_ab) (1 - cos theta_ab) Omega. Formed in their final
+// places: neighbouring rows share bin a, and no permutation of finished rows follows (forming
+// them from the table's slots and moving them took 1.7 ms for 8e6 rows).
+__global__ void __launch_bounds__(256) k_st_features(
+    const unsigned long long *__restrict__ key, const uint32_t *__restrict__ rows,
+    const double *__restrict__ om_in, int64_t n, int64_t n_t_bins,
+    const double *__restrict__ q_sums, const double *__restrict__ t_sums, double vol,
+    float *__restrict__ x, double *__restrict__ y0, long long *__restrict__ key_out) {
+    const int64_t row = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (row >= n) return;
+    const int64_t k = (int64_t)key[row];
+    const double om = om_in[rows[row]];
+    const int64_t a = k / n_t_bins, b = k - a * n_t_bins;
+    const double *sa = q_sums + kStSums * a, *sb = t_sums + kStSums * b;
+    const double Ea = sa[1] / sa[0], Eb = sb[1] / sb[0];
+    const double ua[3] = {sa[2], sa[3], sa[4]}, ub[3] = {sb[2], sb[3], sb[4]};
+    const double na = sqrt((ua[0] * ua[0] + ua[1] * ua[1]) + ua[2] * ua[2]);
+    const double nb = sqrt((ub[0] * ub[0] + ub[1] * ub[1]) + ub[2] * ub[2]);
+    const double cth = ((ua[0] * ub[0] + ua[1] * ub[1]) + ua[2] * ub[2]) / (na * nb);
+    const double qf = fmax(1.0 - cth, 1e-300);
+    const double s = ((Ea * Eb) * qf) / (2.0 * kMe * kMe);
+    const double ra = sa[0] / vol, rb = sb[0] / vol;
+    float *f = x + kMlpIn * row;
+    f[0] = (float)log(Ea);
+    f[1] = (float)log(Eb);
+    f[2] = (float)log(qf);
+    f[3] = (float)log(ra);
+    f[4] = (float)log(rb);
+    f[5] = (float)log(om);
+    y0[row] = ((ra * rb) * bw_sigma(s)) * qf * om;
+    key_out[row] = k;
 }
 
 // Training targets log((Y + eps Y0) / Y0), Y the exact yield of the row's bin pair (0 when
@@ -1023,30 +1044,6 @@ __global__ void k_st_mask_bins(const int32_t *__restrict__ bins, int64_t n,
     out[i] = (b >= 0 && mark[b]) ? b : -1;
 }
 
-// Sort input of the feature rows: key copy and row index.
-__global__ void k_st_keys_iota(const long long *__restrict__ key, int64_t n,
-                               unsigned long long *__restrict__ k, uint32_t *__restrict__ v) {
-    const int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (r >= n) return;
-    k[r] = (unsigned long long)key[r];
-    v[r] = (uint32_t)r;
-}
-
-// Feature rows in the sorted order: row r of the output is row perm[r] of the input.
-__global__ void k_st_permute_rows(const float *__restrict__ x, const double *__restrict__ y0,
-                                  const long long *__restrict__ key,
-                                  const uint32_t *__restrict__ perm, int64_t n,
-                                  float *__restrict__ xo, double *__restrict__ y0o,
-                                  long long *__restrict__ keyo) {
-    const int64_t r = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (r >= n) return;
-    const int64_t s = perm[r];
-#pragma unroll
-    for (int f = 0; f < kMlpIn; ++f) xo[kMlpIn * r + f] = x[kMlpIn * s + f];
-    y0o[r] = y0[s];
-    keyo[r] = key[s];
-}
-
 __global__ void k_fill_i64v(long long *p, long long v, int64_t n) {
     const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (i < n) p[i] = v;
@@ -1056,20 +1053,6 @@ inline unsigned grid_for(int64_t n, int block) { return (unsigned)((n + block - 
 
 }  // namespace
 
-void launch_st_keys_iota(const long long *key, int64_t n, unsigned long long *k, uint32_t *v,
-                         hipStream_t st) {
-    if (n <= 0) return;
-    hipLaunchKernelGGL(k_st_keys_iota, dim3(grid_for(n, 256)), dim3(256), 0, st, key, n, k, v);
-}
-
-void launch_st_permute_rows(const float *x, const double *y0, const long long *key,
-                            const uint32_t *perm, int64_t n, float *xo, double *y0o,
-                            long long *keyo, hipStream_t st) {
-    if (n <= 0) return;
-    hipLaunchKernelGGL(k_st_permute_rows, dim3(grid_for(n, 256)), dim3(256), 0, st, x, y0, key,
-                       perm, n, xo, y0o, keyo);
-}
-
 void launch_st_records(const double *sums, int64_t n_bins, double t_bin, double *soa, int64_t cap,
                        int32_t *rec_bin, unsigned long long *count, hipStream_t st) {
     if (n_bins <= 0) return;
@@ -1077,12 +1060,19 @@ void launch_st_records(const double *sums, int64_t n_bins, double t_bin, double 
                        t_bin, soa, cap, rec_bin, count);
 }
 
-void launch_st_features(const long long *keys, const double *vals, int64_t cap, int64_t n_t_bins,
-                        const double *q_sums, const double *t_sums, double vol, float *x,
-                        double *y0, long long *key_out, int64_t out_cap, unsigned long long *count,
-                        hipStream_t st) {
-    hipLaunchKernelGGL(k_st_features, dim3(grid_for(cap, 256 * kFeatSlots)), dim3(256), 0, st, keys, vals, cap,
-                       n_t_bins, q_sums, t_sums, vol, x, y0, key_out, out_cap, count);
+void launch_st_compact(const long long *keys, const double *vals, int64_t n_slots,
+                       unsigned long long *key, uint32_t *row, double *om, int64_t cap,
+                       unsigned long long *count, hipStream_t st) {
+    hipLaunchKernelGGL(k_st_compact, dim3(grid_for(n_slots, 256 * kCompactSlots)), dim3(256), 0, st,
+                       keys, vals, n_slots, key, row, om, cap, count);
+}
+
+void launch_st_features(const unsigned long long *key, const uint32_t *rows, const double *om,
+                        int64_t n, int64_t n_t_bins, const double *q_sums, const double *t_sums,
+                        double vol, float *x, double *y0, long long *key_out, hipStream_t st) {
+    if (n <= 0) return;
+    hipLaunchKernelGGL(k_st_features, dim3(grid_for(n, 256)), dim3(256), 0, st, key, rows, om, n,
+                       n_t_bins, q_sums, t_sums, vol, x, y0, key_out);
 }
 
 void launch_st_targets(const long long *key, const double *y0, int64_t n, const long long *tkeys,

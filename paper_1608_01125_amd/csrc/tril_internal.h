@@ -559,17 +559,14 @@ void launch_st_bin(const BeamDev &b, const StGridDev &g, int32_t *bins, double *
                    hipStream_t st);
 void launch_st_records(const double *sums, int64_t n_bins, double t_bin, double *soa, int64_t cap,
                        int32_t *rec_bin, unsigned long long *count, hipStream_t st);
-void launch_st_features(const long long *keys, const double *vals, int64_t cap, int64_t n_t_bins,
-                        const double *q_sums, const double *t_sums, double vol, float *x,
-                        double *y0, long long *key_out, int64_t out_cap, unsigned long long *count,
-                        hipStream_t st);
-// Feature rows in ascending key order (a deterministic order: the rows are appended in
-// the order threads claim slots): sort input, then the permutation of the rows.
-void launch_st_keys_iota(const long long *key, int64_t n, unsigned long long *k, uint32_t *v,
-                         hipStream_t st);
-void launch_st_permute_rows(const float *x, const double *y0, const long long *key,
-                            const uint32_t *perm, int64_t n, float *xo, double *y0o,
-                            long long *keyo, hipStream_t st);
+// Feature rows: the table's occupied slots compacted (in no order: threads claim them in none),
+// sorted by key (a deterministic order), then formed in that order.
+void launch_st_compact(const long long *keys, const double *vals, int64_t n_slots,
+                       unsigned long long *key, uint32_t *row, double *om, int64_t cap,
+                       unsigned long long *count, hipStream_t st);
+void launch_st_features(const unsigned long long *key, const uint32_t *rows, const double *om,
+                        int64_t n, int64_t n_t_bins, const double *q_sums, const double *t_sums,
+                        double vol, float *x, double *y0, long long *key_out, hipStream_t st);
 void launch_st_targets(const long long *key, const double *y0, int64_t n, const long long *tkeys,
                        const double *tvals, int64_t tcap, double eps, float *target, double *y_exact,
                        hipStream_t st);

@@ -649,10 +649,12 @@ def tril_dbg_st_audit_sample(ctx, side: int, cap: int):
 def tril_st_features(ctx, q_sums, q_grid, t_sums, t_grid, k0: int, n_steps: int, params=None,
                      cap: int = 1 << 20):
     """Feature rows of the candidate bin pairs: (x [n, 6] float32, y0 [n] float64,
-    key [n] int64), device tensors; grows the buffers once if cap is too small."""
+    key [n] int64), device tensors; grows the buffers once if cap is too small (the first
+    attempt has room for 2^23 rows at least: a second one repeats the pass over the cells)."""
     import torch
     gq, gt = st_grid(q_grid), st_grid(t_grid)
     p = params or sur_params()
+    cap = max(int(cap), 1 << 23)
     for _ in range(2):
         x = torch.empty((max(cap, 1), 6), dtype=torch.float32, device="cuda")
         y0 = torch.empty(max(cap, 1), dtype=torch.float64, device="cuda")
