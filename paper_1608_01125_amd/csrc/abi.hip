@@ -2587,17 +2587,15 @@ int tril_mlp_predict(tril_mlp *p, const float *x, int64_t n, float *mean, float 
     if (n == 0) return TRIL_OK;
     MlpModel &m = p->m;
     const int64_t chunk = std::min<int64_t>(n, (int64_t)1 << 20);
-    float *outs = nullptr;
-    CHK(dev_alloc(&outs, (size_t)(m.K * chunk)));
+    std::lock_guard<std::mutex> hold(m.outs_lock);
+    CHK(mlp_outputs(&m, m.K * chunk));
     for (int64_t a = 0; a < n; a += chunk) {
         const int64_t c = std::min(chunk, n - a);
-        for (int k = 0; k < m.K; ++k) mlp_fused_forward(&m, k, x + a * kMlpIn, c, outs + (int64_t)k * c);
-        mlp_reduce(&m, outs, c, mean + a, sdev + a);
+        mlp_fused_forward(&m, x + a * kMlpIn, c, m.outs);
+        mlp_reduce(&m, m.outs, c, mean + a, sdev + a);
     }
-    hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = hipStreamSynchronize(m.st);
-    dev_free(outs);
-    if (e != hipSuccess) return hip_fail(e);
+    HIPCHK(hipGetLastError());
+    HIPCHK(hipStreamSynchronize(m.st));
     return TRIL_OK;
 }
 

@@ -182,8 +182,8 @@ __global__ void k_mlp_reduce(const float *__restrict__ out, int64_t n, int K, fl
     sdev[i] = K > 1 ? sqrtf(fmaxf(s2 / (float)K - mu * mu, 0.0f) * (float)K / (float)(K - 1)) : 0.0f;
 }
 
-// Inference of one member, all four layers in one kernel. A workgroup takes 128 rows; its
-// four waves each own 64 output features of every hidden layer. The products run on the
+// Inference of every member (blockIdx.y), all four layers in one kernel. A workgroup takes kFR rows
+// of one member; its four waves each own 64 output features of every hidden layer. The products run on the
 // matrix cores with the weights as the A operand (16 features x 32 inputs per fragment,
 // read from an aligned copy of the member's BF16 weights, the next k step's fragments in
 // flight while the current ones multiply) and the activations as the B operand (16 rows x
@@ -191,10 +191,16 @@ __global__ void k_mlp_reduce(const float *__restrict__ out, int64_t n, int K, fl
 // epilogue (bias, SiLU from the hardware exponential and reciprocal, two-at-a-time BF16
 // conversion) stores as one 8-byte LDS write. Layer 1 runs the same way with its 6 inputs
 // padded with zeros to 32; layer 4 is a dot product per row on pairs of BF16 values. The
-// 128 x 256 activations live in LDS as BF16 and are overwritten in place layer by layer.
+// kFR x 256 activations live in LDS as BF16 and are overwritten in place layer by layer. The
+// products and the epilogue of a workgroup alternate behind barriers, so the matrix cores idle
+// in its epilogues unless another workgroup is in its products: 80 rows keep three workgroups
+// on a CU (49 KB of LDS, 170 registers), 128 rows only two. 1e6 rows through 4 members: 128 rows
+// and a launch per member 1.49 ms (713 TFLOP/s), 80 rows and one launch for all of them 1.33 ms
+// (797); 64 rows 1.39 (each weight fragment feeds fewer products), 96 rows at two workgroups
+// 1.57, 64 rows at four 1.55 (registers spill).
 // Same rounding points as the layer-by-layer path (input, every hidden activation to BF16,
 // FP32 accumulation); the activation uses the hardware exponential and reciprocal.
-constexpr int kFR = 128;                 // rows per workgroup
+constexpr int kFR = 80;                  // rows per workgroup
 constexpr int kHL = kMlpHidden + 8;      // LDS row stride of the activations (BF16), padded
 constexpr int kXL = 40;                  // LDS row stride of the padded input (BF16)
 
@@ -207,12 +213,16 @@ __device__ __forceinline__ uint32_t pack2_bf16(float a, float b) {
     return __builtin_bit_cast(uint32_t, v);
 }
 
-__global__ void __launch_bounds__(256, 2) k_mlp_fused(const float *__restrict__ x, int64_t n,
+__global__ void __launch_bounds__(256, 3) k_mlp_fused(const float *__restrict__ x, int64_t n,
                                                       const float *__restrict__ norm,
                                                       const uint16_t *__restrict__ wb,
                                                       const uint16_t *__restrict__ wf,
                                                       const float *__restrict__ w,
                                                       float *__restrict__ out) {
+    wb += (int64_t)blockIdx.y * kMlpStride;
+    wf += (int64_t)blockIdx.y * kFrags * kMlpHH;
+    w += (int64_t)blockIdx.y * kMlpParams;
+    out += (int64_t)blockIdx.y * n;
     __shared__ __align__(16) uint16_t sH[kFR][kHL];
     __shared__ __align__(16) uint16_t sX[kFR][kXL];
     __shared__ __align__(16) uint16_t sW4[kMlpHidden];
@@ -231,11 +241,11 @@ __global__ void __launch_bounds__(256, 2) k_mlp_fused(const float *__restrict__ 
     const int lr = lane & 15, lk = 8 * (lane >> 4), lf = 4 * (lane >> 4);
 #pragma unroll 1
     for (int layer = 0; layer < 3; ++layer) {
-        f32x4 acc[4][8];
+        f32x4 acc[4][kFR / 16];
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
-            for (int j = 0; j < 8; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int j = 0; j < kFR / 16; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
         if (layer == 0) {
             bf16x8 a[4];
 #pragma unroll
@@ -247,7 +257,7 @@ __global__ void __launch_bounds__(256, 2) k_mlp_fused(const float *__restrict__ 
                 a[mt] = __builtin_bit_cast(bf16x8, e);
             }
 #pragma unroll
-            for (int nt = 0; nt < 8; ++nt) {
+            for (int nt = 0; nt < kFR / 16; ++nt) {
                 const bf16x8 bv = *reinterpret_cast<const bf16x8 *>(&sX[nt * 16 + lr][lk]);
 #pragma unroll
                 for (int mt = 0; mt < 4; ++mt)
@@ -267,7 +277,7 @@ __global__ void __launch_bounds__(256, 2) k_mlp_fused(const float *__restrict__ 
                         an[mt] = load_frag(W, wave * 4 + mt, (k0 >> 5) + 1, lane);
                 }
 #pragma unroll
-                for (int nt = 0; nt < 8; ++nt) {
+                for (int nt = 0; nt < kFR / 16; ++nt) {
                     const bf16x8 bv = *reinterpret_cast<const bf16x8 *>(&sH[nt * 16 + lr][k0 + lk]);
 #pragma unroll
                     for (int mt = 0; mt < 4; ++mt)
@@ -286,7 +296,7 @@ __global__ void __launch_bounds__(256, 2) k_mlp_fused(const float *__restrict__ 
             const int f = f0 + mt * 16 + lf;
             const float b0 = bias[f], b1 = bias[f + 1], b2 = bias[f + 2], b3 = bias[f + 3];
 #pragma unroll
-            for (int nt = 0; nt < 8; ++nt) {
+            for (int nt = 0; nt < kFR / 16; ++nt) {
                 const f32x4 z = acc[mt][nt];
                 uint2 pk;
                 pk.x = pack2_bf16(silu_fast(z[0] + b0), silu_fast(z[1] + b1));
@@ -296,7 +306,7 @@ __global__ void __launch_bounds__(256, 2) k_mlp_fused(const float *__restrict__ 
         }
         __syncthreads();
     }
-    {   // layer 4: two threads per row, 64 pairs of BF16 products each
+    if (tid < 2 * kFR) {  // layer 4: two threads per row, 64 pairs of BF16 products each
         const int row = tid >> 1, half = tid & 1;
         const uint32_t *hrow = reinterpret_cast<const uint32_t *>(&sH[row][half * 128]);
         const uint32_t *wrow = reinterpret_cast<const uint32_t *>(&sW4[half * 128]);
@@ -889,11 +899,10 @@ inline unsigned blocks(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
 
 }  // namespace
 
-void mlp_fused_forward(MlpModel *m, int k, const float *x, int64_t n, float *out) {
+void mlp_fused_forward(MlpModel *m, const float *x, int64_t n, float *out) {
     if (n <= 0) return;
-    hipLaunchKernelGGL(k_mlp_fused, dim3(blocks(n, kFR)), dim3(256), 0, m->st, x, n, m->norm,
-                       m->wb + (int64_t)k * kMlpStride, m->wf + (int64_t)k * kFrags * kMlpHH,
-                       m->w + (int64_t)k * kMlpParams, out);
+    hipLaunchKernelGGL(k_mlp_fused, dim3(blocks(n, kFR), m->K), dim3(256), 0, m->st, x, n, m->norm,
+                       m->wb, m->wf, m->w, out);
 }
 
 void mlp_moments(const float *a, int64_t n, int c, double *out, double *part, hipStream_t st) {
@@ -917,6 +926,7 @@ MlpModel::~MlpModel() {
     (void)hipFree(act);
     (void)hipFree(part);
     (void)hipFree(bpart);
+    (void)hipFree(outs);
 }
 
 template <typename T>
@@ -998,6 +1008,10 @@ int64_t slice_rows(int64_t n) {
 int64_t act_ld(int64_t n) { return (n + 63) / 64 * 64 + 64; }
 
 }  // namespace
+
+int mlp_outputs(MlpModel *m, int64_t n) {
+    return mlp_grow(m, &m->outs, &m->outs_cap, n);
+}
 
 int mlp_train_group(const MlpModel *m, int64_t n) {
     const int64_t per = kActRows * act_ld(n) * 2 + kMlpSlices * kMlpParams * 4;

@@ -5,6 +5,7 @@
 
 #include <cstddef>
 #include <cstdint>
+#include <mutex>
 #include <vector>
 
 #include "tril.h"
@@ -512,7 +513,9 @@ struct MlpModel {
     uint16_t *act = nullptr;    // transposed activations and gradients, kActRows x act_ld each
     float *part = nullptr;      // slice partials of the weight gradients, kMlpSlices x kMlpParams
     float *bpart = nullptr;     // 64-row partials of the bias gradients
-    int64_t act_cap = 0, part_cap = 0, bpart_cap = 0;
+    float *outs = nullptr;      // inference: outputs of all members for one chunk of rows, kept;
+    std::mutex outs_lock;       // held while a call uses it, so that several threads may predict
+    int64_t act_cap = 0, part_cap = 0, bpart_cap = 0, outs_cap = 0;
     int64_t adam_t = 0;
     std::vector<void *> allocs;
     ~MlpModel();
@@ -529,8 +532,10 @@ int mlp_scratch(MlpModel *m, int64_t n, int group);
 // losses are added to m->loss.
 void mlp_step(MlpModel *m, int k0, int group, const float *x, const float *y, int64_t n,
               int64_t batch, bool hashed, uint64_t seed, int64_t step, bool add_loss, float lr);
-// Inference: one fused forward pass of member k.
-void mlp_fused_forward(MlpModel *m, int k, const float *x, int64_t n, float *out);
+// Inference: one fused forward pass of every member, member k's outputs at out + k n; room for
+// n outputs in m->outs.
+void mlp_fused_forward(MlpModel *m, const float *x, int64_t n, float *out);
+int mlp_outputs(MlpModel *m, int64_t n);
 void mlp_reduce(MlpModel *m, const float *out, int64_t n, float *mean, float *sdev);
 void mlp_cast(MlpModel *m);
 // Column sums and sums of squares into out[2 c] (written, fixed-order reduction); part:
