@@ -583,6 +583,10 @@ int32_t descent_window(const tril_ctx *c, int32_t win) {
     return std::min(std::min(d, win), kMaxDescent);
 }
 
+// Sheared boxes widen each axis by one step's motion along the shear's axis, which a descent of
+// fewer steps would not win back.
+constexpr int32_t kShearSteps = 3;
+
 // Automatic descent length. A longer descent loads fewer nodes per step but reaches more
 // leaves (its hull stretches along the motion), each tested at every step in range. From the
 // leaf tests per descent L since the last adaptation: above kAdaptHigh the length halves
@@ -613,7 +617,10 @@ void adapt_descent(tril_ctx *c, int64_t checks, int64_t queries) {
 // rows by their Morton codes at the batch's key step, the tree shape emitted from that
 // order, and its copies (one per step, or one per window of steps) filled with the boxes
 // of their steps.
-int enqueue_build(tril_ctx *c, hipStream_t st, bool timed, bool presorted = false) {
+// q_stats: the statistics of the one query beam that will meet this build (nullptr: not known
+// yet, as in a build of its own), for the shear of the four-child forms.
+int enqueue_build(tril_ctx *c, hipStream_t st, bool timed, bool presorted = false,
+                  const InstStats *q_stats = nullptr) {
     const BeamDev &t = c->tgt;
     const int64_t n = t.n;
     const int32_t win = build_window(c, t.m);
@@ -645,9 +652,12 @@ int enqueue_build(tril_ctx *c, hipStream_t st, bool timed, bool presorted = fals
     c->n_int = n > 0 ? (int64_t)copies * (n - 1) : -1;
     c->tgt_cloud = c->cloud;
     c->tgt_dt = c->box_dt;
-    if (win > 1) launch_win_bounds(c->t_stats, t.n_inst, c->dt, c->t_wb, st);
     c->quad = win > 1 && n > 1 && (int64_t)copies * (n - 1) <= c->nodes4_cap &&
               copies <= c->frames_cap && n - 1 <= c->inside_cap;
+    const bool shear = q_stats != nullptr && c->quad && !c->keep_nodes &&
+                       descent_window(c, win) >= kShearSteps;
+    if (win > 1)
+        launch_win_bounds(c->t_stats, t.n_inst, c->dt, shear ? q_stats : nullptr, c->t_wb, st);
     launch_inst_roots(t, c->cloud, c->box_dt, c->inst_base, rows, c->inst_root, c->root_box, c->d_cnt,
                       st, win, c->t_rec);
     int32_t *xbase = nullptr;
@@ -658,11 +668,11 @@ int enqueue_build(tril_ctx *c, hipStream_t st, bool timed, bool presorted = fals
     }
     // four-child forms: the frames first; the refit forms the nodes whose descendants lie in
     // one of its chunks, the collapse the others
-    if (c->quad) launch_win_frames(c->t_stats, t.n_inst, c->dt, win, t.m, c->d_cnt, c->t_frames, st);
+    if (c->quad) launch_win_frames(c->t_stats, t.n_inst, c->dt, win, t.m, c->d_cnt, c->t_wb, c->t_frames, st);
     launch_refit(t, c->cloud, c->box_dt, rows, c->prec, c->nflags, c->nodes, c->refit_slots,
                  c->refit_slot_cap, xbase, xalt, c->d_cnt, &c->d_cnt->err, st, win, c->t_rec,
                  c->quad ? c->t_frames : nullptr, c->quad ? c->nodes4 : nullptr,
-                 c->quad ? c->t_inside : nullptr, c->keep_nodes);
+                 c->quad ? c->t_inside : nullptr, c->keep_nodes, shear ? c->t_wb : nullptr);
     c->nodes_partial = c->quad && !c->keep_nodes;
     if (c->quad)
         launch_collapse4(c->nodes, n, copies, c->t_frames, c->nodes4, &c->d_cnt->err, st,
@@ -1275,7 +1285,7 @@ int tril_run(tril_ctx *c, const tril_beam *t, const tril_beam *q, int32_t k0, in
         // copy and the run's statistics, and writes only query buffers
         HIPCHK(hipEventRecord(c->ev_qfork, st));
         HIPCHK(hipStreamWaitEvent(c->qst, c->ev_qfork, 0));
-        CHK(enqueue_build(c, st, tm, pre));
+        CHK(enqueue_build(c, st, tm, pre, c->q_stats));
         if (!sort) {
             c->q_order = nullptr;  // the working copy is already in Morton order
             c->q_order_len = 0;
@@ -1352,7 +1362,8 @@ int tril_run(tril_ctx *c, const tril_beam *t, const tril_beam *q, int32_t k0, in
                 (const void *)(intptr_t)c->trav_queue,
                 (const void *)(intptr_t)c->cand_cap, (const void *)(intptr_t)c->kwin,
                 (const void *)(intptr_t)c->kdesc, (const void *)(intptr_t)c->kdesc_auto,
-                (const void *)(intptr_t)regather, (const void *)(intptr_t)pre};
+                (const void *)(intptr_t)regather, (const void *)(intptr_t)pre,
+                (const void *)(intptr_t)c->keep_nodes};
             int slot = -1;
             for (int g = 0; g < tril_ctx::kGraphs && slot < 0; ++g)
                 if (c->gexec[g] && key == c->gkey[g]) slot = g;

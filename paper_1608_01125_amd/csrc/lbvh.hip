@@ -660,19 +660,54 @@ __global__ void k_inst_roots(BeamDev b, CloudBox cloud, double dt,
 // Per target instance: bounds of u dt as the refit rounds it ((float)(dt u), FP64 product
 // then nearest FP32; both roundings are monotone, so the rounded bounds bound every
 // photon's), widened by one FP32 step outward.
+// q_stats (or nullptr: unsheared boxes): the query beam's statistics. An axis is sheared where
+// the relative motion along it exceeds the two beams' spread of directions, below which the
+// hull would not become thinner; coordinates near the end of the FP32 range are left alone.
 __global__ void k_win_bounds(const InstStats *__restrict__ stats, int32_t n_inst, double dt,
-                             WinBound *__restrict__ vb) {
+                             const InstStats *__restrict__ q_stats, WinBound *__restrict__ vb) {
     const int32_t mi = blockIdx.x * blockDim.x + threadIdx.x;
     if (mi >= n_inst) return;
+    float sh[3] = {0.0f, 0.0f, 0.0f};
+    int32_t k = 0;
+    const InstStats &ts = stats[mi];
+    if (q_stats != nullptr && ts.mn[0] <= ts.mx[0] && q_stats[mi].mn[0] <= q_stats[mi].mx[0]) {
+        double rel[3], spread[3], top = fabs(dt) * 0x1p32;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const double tl = ord2d(ts.mn[3 + a]), th = ord2d(ts.mx[3 + a]);
+            const double ql = ord2d(q_stats[mi].mn[3 + a]), qh = ord2d(q_stats[mi].mx[3 + a]);
+            rel[a] = 0.5 * (ql + qh) - 0.5 * (tl + th);
+            spread[a] = 0.5 * (qh - ql) + 0.5 * (th - tl);
+            top = fmax(top, fabs(dt) * 0x1p32 * fmax(fmax(fabs(tl), fabs(th)), fmax(fabs(ql), fabs(qh))));
+            top = fmax(top, fmax(fabs(ord2d(ts.mn[a])), fabs(ord2d(ts.mx[a]))));
+            top = fmax(top, fmax(fabs(ord2d(q_stats[mi].mn[a])), fabs(ord2d(q_stats[mi].mx[a]))));
+        }
+        k = fabs(rel[1]) > fabs(rel[0]) ? 1 : 0;
+        if (fabs(rel[2]) > fabs(rel[k])) k = 2;
+        if (top < 1e30)
+#pragma unroll
+            for (int a = 0; a < 3; ++a)
+                if (a != k && fabs(rel[a]) > spread[a]) sh[a] = (float)(rel[a] / rel[k]);
+    }
     float lo[3], hi[3];
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         lo[a] = nextafterf((float)(dt * ord2d(stats[mi].mn[3 + a])), -INFINITY);
         hi[a] = nextafterf((float)(dt * ord2d(stats[mi].mx[3 + a])), INFINITY);
     }
+    const double kl = k == 0 ? lo[0] : (k == 1 ? lo[1] : lo[2]);
+    const double kh = k == 0 ? hi[0] : (k == 1 ? hi[1] : hi[2]);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        if (sh[a] == 0.0f) continue;
+        const double e = sh[a] * kl, f = sh[a] * kh;
+        lo[a] = nextafterf((float)(lo[a] - fmax(e, f)), -INFINITY);
+        hi[a] = nextafterf((float)(hi[a] - fmin(e, f)), INFINITY);
+    }
     WinBound o;
     o.lo = make_float4(lo[0], lo[1], lo[2], 0.0f);
     o.hi = make_float4(hi[0], hi[1], hi[2], 0.0f);
+    o.shear = make_float4(sh[0], sh[1], sh[2], __int_as_float(k));
     vb[mi] = o;
 }
 
@@ -682,7 +717,7 @@ __global__ void k_win_bounds(const InstStats *__restrict__ stats, int32_t n_inst
 // a margin eight times the rounding of the FP32 leaf boxes (below 2^-19 (|x| + m dt)).
 __global__ void k_win_frames(const InstStats *__restrict__ stats, int32_t n_inst, double dt,
                              int32_t win, int32_t m, const DevCounters *__restrict__ c,
-                             WinFrame *__restrict__ frames) {
+                             const WinBound *__restrict__ vb, WinFrame *__restrict__ frames) {
     const int32_t cp = blockIdx.x * blockDim.x + threadIdx.x;
     if (cp >= window_copies(m, win)) return;
     const int32_t r = window_ref_step(cp, win, m);
@@ -691,13 +726,33 @@ __global__ void k_win_frames(const InstStats *__restrict__ stats, int32_t n_inst
     for (int32_t mi = 0; mi < n_inst; ++mi) {
         const InstStats &st = stats[mi];
         if (st.mn[0] > st.mx[0]) continue;  // no usable photon
+        double il[3], ih[3];
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
             const double ul = ord2d(st.mn[3 + a]), uh = ord2d(st.mx[3 + a]);
             const double e = fmin(fmin(ul * t0, ul * t1), fmin(uh * t0, uh * t1));
             const double f = fmax(fmax(ul * t0, ul * t1), fmax(uh * t0, uh * t1));
-            lo[a] = fmin(lo[a], ord2d(st.mn[a]) + e);
-            hi[a] = fmax(hi[a], ord2d(st.mx[a]) + f);
+            il[a] = ord2d(st.mn[a]) + e;
+            ih[a] = ord2d(st.mx[a]) + f;
+        }
+        // sheared boxes lie in the sheared interval, whose ends |a| <= 1 leaves below the sum
+        // of the magnitudes that the margin below is a fraction of
+        const float4 sh = vb[mi].shear;
+        const int32_t k = __float_as_int(sh.w);
+        const double kl = k == 0 ? il[0] : (k == 1 ? il[1] : il[2]);
+        const double kh = k == 0 ? ih[0] : (k == 1 ? ih[1] : ih[2]);
+        const double sa[3] = {sh.x, sh.y, sh.z};
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            double mg = 0.0;
+            if (sa[a] != 0.0) {
+                const double e = sa[a] * kl, f = sa[a] * kh;
+                il[a] -= fmax(e, f);
+                ih[a] -= fmin(e, f);
+                mg = 0x1p-16 * (fmax(fabs(kl), fabs(kh)) + (double)m * dt);
+            }
+            lo[a] = fmin(lo[a], il[a] - mg);
+            hi[a] = fmax(hi[a], ih[a] + mg);
         }
     }
     float base[3], inv[3];
@@ -971,7 +1026,8 @@ __global__ void __launch_bounds__(kRefitChunk, 8) k_refit(BeamDev b, CloudBox cl
                                                     const WinFrame *__restrict__ frames,
                                                     CNode4 *__restrict__ nodes4,
                                                     uint8_t *__restrict__ inside_flag,
-                                                    int32_t store_inner) {
+                                                    int32_t store_inner,
+                                                    const WinBound *__restrict__ vb) {
     // halves of the chunk's nodes as their parents hold them, lo (xyz, link) and hi
     // (xyz, energy bound): [0, chunk) internal node c0 + k, [chunk, 2 chunk) leaf c0 + k
     // (before the first step the same memory holds the nodes' heights)
@@ -1064,12 +1120,14 @@ __global__ void __launch_bounds__(kRefitChunk, 8) k_refit(BeamDev b, CloudBox cl
     ph.x = ph.y = ph.z = ph.ux = ph.uy = ph.uz = 0.0;
     float eup = 0.0f;  // the leaf's energy rounded up: the subtree bound of the prune
     LeafMotion lm = {};
+    int32_t mi = 0;  // the row's instance (sheared boxes)
     if (in) {
         row = rows[j];
         double E, w;
         ph = load_photon(b, row, E, w);
         eup = ph.ok ? f32_up(E) : 0.0f;
         if (kMoved) lm = leaf_motion(ph, (double)step0 * dt, dt, cloud);
+        if (kMoved && vb != nullptr && b.n_inst > 1) mi = find_inst(b.inst_off, b.n_inst, row);
         if (kMoved && win > 1 && group == 0) {
             float4 *o = reinterpret_cast<float4 *>(trec + j);
             o[0] = make_float4(lm.l0[0], lm.l0[1], lm.l0[2], __int_as_float((int32_t)row));
@@ -1087,6 +1145,7 @@ __global__ void __launch_bounds__(kRefitChunk, 8) k_refit(BeamDev b, CloudBox cl
             float lo[3], hi[3];
             if (kMoved) {
                 leaf_box_moved(lm, ok, window_ref_step(step, win, b.m), lo, hi);
+                if (vb != nullptr && ok) shear_box(vb[mi].shear, lo, hi);
             } else {
                 float cen[3];
                 photon_box(ph, (double)(step0 + (unsigned)step) * dt, dt, cloud, 0.0, lo, hi, cen);
@@ -1484,11 +1543,11 @@ void launch_inst_roots(const BeamDev &b, const CloudBox &cloud, double dt, const
 }
 
 void launch_win_frames(const InstStats *stats, int32_t n_inst, double dt, int32_t win, int32_t m,
-                       const DevCounters *c, WinFrame *frames, hipStream_t st) {
+                       const DevCounters *c, const WinBound *vb, WinFrame *frames, hipStream_t st) {
     const int32_t nc = window_copies(m, win);
     if (nc <= 0) return;
     hipLaunchKernelGGL(k_win_frames, dim3(grid_for(nc, 64)), dim3(64), 0, st, stats, n_inst, dt,
-                       win, m, c, frames);
+                       win, m, c, vb, frames);
 }
 
 void launch_collapse4(const Node *nodes, int64_t n, int32_t copies, const WinFrame *frames,
@@ -1501,11 +1560,11 @@ void launch_collapse4(const Node *nodes, int64_t n, int32_t copies, const WinFra
                        dim3(256), 0, st, nodes, n, copies, frames, out, err, inside);
 }
 
-void launch_win_bounds(const InstStats *stats, int32_t n_inst, double dt, WinBound *vb,
-                       hipStream_t st) {
+void launch_win_bounds(const InstStats *stats, int32_t n_inst, double dt,
+                       const InstStats *q_stats, WinBound *vb, hipStream_t st) {
     if (n_inst <= 0) return;
     hipLaunchKernelGGL(k_win_bounds, dim3(grid_for(n_inst, 64)), dim3(64), 0, st, stats, n_inst,
-                       dt, vb);
+                       dt, q_stats, vb);
 }
 
 int64_t refit_slots_needed(int64_t n, int32_t m) {
@@ -1536,7 +1595,7 @@ void launch_refit(const BeamDev &b, const CloudBox &cloud, double dt, const uint
                   const PRec *prec, int32_t *flags, Node *nodes, int32_t *slots, int64_t slot_cap,
                   int32_t *xbase, bool xalt, const DevCounters *c, unsigned int *err,
                   hipStream_t st, int32_t win, TRec *trec, const WinFrame *frames,
-                  CNode4 *nodes4, uint8_t *inside, bool store_inner) {
+                  CNode4 *nodes4, uint8_t *inside, bool store_inner, const WinBound *vb) {
     const int64_t n = b.n;
     if (cloud.on != 0) win = 1;  // window copies need straight-line leaf boxes
     if (win <= 1 || frames == nullptr || inside == nullptr) nodes4 = nullptr;
@@ -1557,11 +1616,12 @@ void launch_refit(const BeamDev &b, const CloudBox &cloud, double dt, const uint
         hipLaunchKernelGGL(k_refit<true>, dim3((unsigned)(chunks * groups)), dim3(kRefitChunk), 0,
                            st, b, cloud, dt, sorted_rows, chunks, group_steps, prec, flags, nodes,
                            slots, levels ? 1 : 0, c, err, win, m, trec, frames, nodes4, inside,
-                           store_inner ? 1 : 0);
+                           store_inner ? 1 : 0, nodes4 != nullptr ? vb : nullptr);
     else
         hipLaunchKernelGGL(k_refit<false>, dim3((unsigned)(chunks * groups)), dim3(kRefitChunk), 0,
                            st, b, cloud, dt, sorted_rows, chunks, group_steps, prec, flags, nodes,
-                           slots, levels ? 1 : 0, c, err, 1, m, trec, nullptr, nullptr, nullptr, 1);
+                           slots, levels ? 1 : 0, c, err, 1, m, trec, nullptr, nullptr, nullptr, 1,
+                           nullptr);
     if (levels) {
         const XLev x = xlev_layout(xbase, n);
         hipLaunchKernelGGL(k_refit_levels, dim3((unsigned)m), dim3(kXThreads), 0, st,

@@ -249,23 +249,42 @@ __device__ __forceinline__ int32_t traverse_query(int64_t q, const Node *__restr
             record_box(a, d, w, (float)(qs + qn - 1), qz);
             qe = d.w;
             const float da = (float)(qs - r), dz = (float)(qs + qn - 1 - r);
-            float4 vlo, vhi;
+            float4 vlo, vhi, sh;
             const int32_t iu = __builtin_amdgcn_readfirstlane(inst);
             if (__ballot(inst == iu) == __ballot(1)) {
                 typedef int v8i __attribute__((ext_vector_type(8)));
+                typedef int v4i __attribute__((ext_vector_type(4)));
                 v8i rv;
+                v4i rs;
                 const WinBound *p = wa.vb + iu;
-                asm volatile("s_load_dwordx8 %0, %1, 0x0\n\ts_waitcnt lgkmcnt(0)"
-                             : "=s"(rv)
+                asm volatile("s_load_dwordx8 %0, %2, 0x0\n\ts_load_dwordx4 %1, %2, 0x20\n\t"
+                             "s_waitcnt lgkmcnt(0)"
+                             : "=&s"(rv), "=&s"(rs)
                              : "s"(p));
                 vlo = make_float4(__int_as_float(rv[0]), __int_as_float(rv[1]),
                                   __int_as_float(rv[2]), __int_as_float(rv[3]));
                 vhi = make_float4(__int_as_float(rv[4]), __int_as_float(rv[5]),
                                   __int_as_float(rv[6]), __int_as_float(rv[7]));
+                sh = make_float4(__int_as_float(rs[0]), __int_as_float(rs[1]),
+                                 __int_as_float(rs[2]), __int_as_float(rs[3]));
             } else {
                 const float4 *vp = reinterpret_cast<const float4 *>(wa.vb + inst);
                 vlo = vp[0];
                 vhi = vp[1];
+                sh = vp[2];
+            }
+            // the slack of each axis, and the two boxes in the instance's sheared coordinates
+            float slk[3];
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+                slk[k] = wslack(fminf(qa[k], qz[k]), fmaxf(qa[k + 3], qz[k + 3]), wa.reach);
+            if ((sh.x != 0.0f) | (sh.y != 0.0f) | (sh.z != 0.0f)) {
+                shear_box(sh, qa, qa + 3);
+                shear_box(sh, qz, qz + 3);
+                const float sk = axis_of(slk[0], slk[1], slk[2], __float_as_int(sh.w));
+                slk[0] += fabsf(sh.x) * sk;
+                slk[1] += fabsf(sh.y) * sk;
+                slk[2] += fabsf(sh.z) * sk;
             }
             float4 fb, fi;
             const int32_t cu = __builtin_amdgcn_readfirstlane(cp);
@@ -291,8 +310,7 @@ __device__ __forceinline__ int32_t traverse_query(int64_t q, const Node *__restr
             for (int k = 0; k < 3; ++k) {
                 const float e1 = da * lo3[k], e2 = da * hi3[k];
                 const float f1 = dz * lo3[k], f2 = dz * hi3[k];
-                const float sl =
-                    wslack(fminf(qa[k], qz[k]), fmaxf(qa[k + 3], qz[k + 3]), wa.reach);
+                const float sl = slk[k];
                 const float wl = fminf((qa[k] - fmaxf(e1, e2)) - sl, (qz[k] - fmaxf(f1, f2)) - sl);
                 const float wh = fmaxf((qa[k + 3] - fminf(e1, e2)) + sl,
                                        (qz[k + 3] - fminf(f1, f2)) + sl);

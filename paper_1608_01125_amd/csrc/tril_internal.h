@@ -185,9 +185,39 @@ static_assert(sizeof(TRec) == 48, "target record layout");
 
 // Bounds of u dt over the photons of one target instance, per axis, as FP32 values the
 // refit's rounding of u dt cannot leave (lo: lowest, hi: highest; .w unused).
+// With sheared node boxes the bounds are those of the sheared motion; shear: the instance's
+// factors a (below; zero along the axis itself) and, as integer bits in .w, the axis.
 struct WinBound {
-    float4 lo, hi;
+    float4 lo, hi, shear;
 };
+
+// Sheared node boxes. A descent's hull holds the query's boxes of several steps in the target's
+// frame, so it stretches along the beams' relative motion: thin where that runs along an axis
+// (head-on beams), but the whole rectangle about a diagonal where it does not. The window
+// copies of a run therefore hold boxes in the coordinates x_i - a_i x_k, k the axis of the
+// largest component of the relative direction of the instance's two beams and a_i its other
+// components over that one, in which the relative motion runs along axis k. The interval of
+// a box in the sheared coordinate is that of all its points, so boxes that meet have sheared
+// boxes that meet: every leaf that the exact test accepts is still reached, and a leaf is
+// still tested against its own box (the candidates do not depend on the shear). Runs of 1.6e7
+// photons per beam crossing at 150 degrees: 445 -> 398 ms; 64 instances at 90 to 180 degrees:
+// 116.4 -> 97.9 ms; head-on beams (no shear) the same.
+__device__ __forceinline__ float axis_of(float x, float y, float z, int32_t k) {
+    return k == 0 ? x : (k == 1 ? y : z);
+}
+
+// The box [lo, hi] in the sheared coordinates.
+__device__ __forceinline__ void shear_box(const float4 sh, float lo[3], float hi[3]) {
+    const int32_t k = __float_as_int(sh.w);
+    const float kl = axis_of(lo[0], lo[1], lo[2], k), kh = axis_of(hi[0], hi[1], hi[2], k);
+    const float a[3] = {sh.x, sh.y, sh.z};
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        const float e = a[i] * kl, f = a[i] * kh;
+        lo[i] -= fmaxf(e, f);
+        hi[i] -= fminf(e, f);
+    }
+}
 
 // What a traversal over window copies needs besides the nodes.
 struct WinArgs {
@@ -215,6 +245,11 @@ __host__ __device__ inline int64_t descent_count(int32_t m, int32_t win, int32_t
 // 1.01 dt + 1e-11 (1 + M): target boxes carry no radius pad), so the rounding of its
 // boxes at s and at the copy's step r, and of the widened box itself, stays below
 // (M + (m + 2) dt) 2^-19: the slack below is at least twice that.
+//
+// In sheared coordinates the slack of axis i is wslack_i + |a_i| wslack_k: the errors above
+// enter with those factors, and forming the sheared intervals of both boxes and of the motion
+// adds at most 8 roundings of 2^-24 of the same magnitudes, below 2^-20 of them, where the
+// half to spare is 2^-19.
 __device__ __forceinline__ float wslack(float ql, float qh, float reach) {
     return (fmaxf(fabsf(ql), fabsf(qh)) + reach) * 0x1p-18f;
 }
@@ -393,9 +428,9 @@ void launch_inst_roots(const BeamDev &b, const CloudBox &cloud, double dt, const
                        const DevCounters *c, hipStream_t st, int32_t win = 1,
                        TRec *trec = nullptr);
 // Quantisation frame of each of the window_copies(m, win) copies of a batch of m steps
-// from the first step (device counter) and the per-instance statistics.
+// from the first step (device counter), the per-instance statistics and shears.
 void launch_win_frames(const InstStats *stats, int32_t n_inst, double dt, int32_t win, int32_t m,
-                       const DevCounters *c, WinFrame *frames, hipStream_t st);
+                       const DevCounters *c, const WinBound *vb, WinFrame *frames, hipStream_t st);
 // Four-child forms of the copies x (n - 1) internal nodes (n rows) of window copies, in their
 // copies' frames; a child box outside its frame, or children that are not a split and its
 // successor, set kErrInternal. inside: NULL, or one byte per internal node of the shape,
@@ -404,9 +439,10 @@ void launch_win_frames(const InstStats *stats, int32_t n_inst, double dt, int32_
 void launch_collapse4(const Node *nodes, int64_t n, int32_t copies, const WinFrame *frames,
                       CNode4 *out, unsigned int *err, hipStream_t st,
                       const uint8_t *inside = nullptr);
-// Per-instance bounds of u dt of a target beam from its statistics (window copies).
-void launch_win_bounds(const InstStats *stats, int32_t n_inst, double dt, WinBound *vb,
-                       hipStream_t st);
+// Per-instance bounds of u dt of a target beam from its statistics (window copies); with the
+// query beam's statistics, its shear and the bounds of the sheared motion.
+void launch_win_bounds(const InstStats *stats, int32_t n_inst, double dt,
+                       const InstStats *q_stats, WinBound *vb, hipStream_t st);
 // Nodes of the b.m steps of view b sharing the shape over its b.n rows, each step's
 // leaf boxes computed from the photons (sorted_rows: row of each sorted position;
 // flags: b.m (b.n - 1) arrival flags, zero on entry and left zero (the second arrival at
@@ -430,13 +466,15 @@ bool enqueue_xlevels(const PRec *prec, int64_t n, int32_t *base, const SortScrat
 // one 512-leaf chunk are written from the chunk's merged boxes, and inside (b.n - 1 bytes)
 // marks those nodes for launch_collapse4, which forms the others. With nodes4 and
 // store_inner false, the binary nodes of the nodes whose parent lies in their chunk too are
-// not stored (nothing reads them once their forms exist).
+// not stored (nothing reads them once their forms exist). With vb the node boxes are formed in
+// each instance's sheared coordinates.
 void launch_refit(const BeamDev &b, const CloudBox &cloud, double dt, const uint32_t *sorted_rows,
                   const PRec *prec, int32_t *flags, Node *nodes, int32_t *slots, int64_t slot_cap,
                   int32_t *xbase, bool xalt, const DevCounters *c, unsigned int *err,
                   hipStream_t st, int32_t win = 1, TRec *trec = nullptr,
                   const WinFrame *frames = nullptr, CNode4 *nodes4 = nullptr,
-                  uint8_t *inside = nullptr, bool store_inner = true);
+                  uint8_t *inside = nullptr, bool store_inner = true,
+                  const WinBound *vb = nullptr);
 
 // n_int: internal nodes of all steps' trees; root_box: box of each combined instance
 // whose root is a leaf; nq: virtual query count (steps x rows).
