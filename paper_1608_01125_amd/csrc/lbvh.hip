@@ -359,6 +359,30 @@ __device__ __forceinline__ void photon_box(const RowPhoton &r, double t, double 
     }
 }
 
+// Energy class in the order of a batch's queries. The threshold prune lets a query of energy E
+// meet only targets above m_e^2 / E, so in beams of a broad spectrum queries side by side
+// descend very different parts of the tree and a wave waits for its most energetic lane. Two
+// bits of y = E E_max / m_e^2 (E_max the largest target energy: y is how far below it the
+// query's partners reach), by octaves from 8, take the place of the code's two lowest bits,
+// above the nine lowest of the rest: a cell's queries of one class, a few waves full, run
+// together and still share the cell's part of the tree. Only queries are ordered so (the order
+// enters no result); classes in the target tree make it reach further for every query of mixed
+// energies. Beams of 1.6e7 photons with E^-2 spectra: 398 -> 373 ms per run; above the 4 to 9
+// lowest bits 0.3% apart, above 13 or more and with three bits 1% and more slower. Where the
+// two beams' largest energies give y < 64 most pairs are above threshold: plain codes.
+constexpr int kClassBits = 2, kClassLow = 9;
+__device__ __forceinline__ uint32_t class_code(uint32_t code, int bits, double E,
+                                               const InstStats &t, const InstStats &self) {
+    const double scale = __longlong_as_double((long long)t.emax) / (kMe * kMe);
+    if (bits < 2 * kClassLow || !(__longlong_as_double((long long)self.emax) * scale >= 64.0))
+        return code;
+    const double y = E * scale;
+    const uint32_t cls = y < 8.0 ? 0u : (y < 16.0 ? 1u : (y < 32.0 ? 2u : 3u));
+    code >>= kClassBits;
+    const uint32_t low = (1u << kClassLow) - 1u;
+    return ((code & ~low) << kClassBits) | (cls << kClassLow) | (code & low);
+}
+
 // Swept box of each virtual element over its step window [t_k, t_k + dt], rounded
 // outward to FP32, and its sort key. Query photons are padded by an upper bound of
 // their collision radius with any photon of the same target instance:
@@ -441,7 +465,9 @@ __global__ void __launch_bounds__(256) k_boxes_keys(BeamDev b, int query, CloudB
             blo[a] = (float)(ord2d(ss.mn[a]) + tau * ord2d(ss.mn[3 + a]));
             bhi[a] = (float)(ord2d(ss.mx[a]) + tau * ord2d(ss.mx[3 + a]));
         }
-        const uint32_t code = morton30(cen, blo, bhi) >> (30 - kl.morton_bits);
+        uint32_t code = morton30(cen, blo, bhi) >> (30 - kl.morton_bits);
+        if (rec != nullptr && query && b.n_inst == 1 && r.ok)
+            code = class_code(code, kl.morton_bits, E, t_stats[0], self_stats[0]);
         if (kWide)
             keys64[i] = ((unsigned long long)(uint32_t)mi << kl.prefix_shift) | code;
         else
