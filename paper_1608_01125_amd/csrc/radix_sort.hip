@@ -27,7 +27,10 @@ constexpr int kWaves = kBlock / 64;
 constexpr int kItems = 16;
 constexpr int kTile = kBlock * kItems;  // 4096 keys per tile
 constexpr int kItemsMid = 4;
-constexpr int64_t kMidSort = (int64_t)1 << 18;
+// 240 tiles of 1024: their status words of eight passes stay under 2 MiB, where an allocation
+// becomes much dearer (at 2^18 keys the two scratches of a context's first run of 1e6 photons
+// cost it 1.5 ms).
+constexpr int64_t kMidSort = (int64_t)240 * kBlock * kItemsMid;
 // One workgroup is the faster while its passes, about 0.8 us per thousand keys and pass on top of
 // 2 us, stay below a launch of tiles (8 us, one round of them). Three passes: 10 us at 2000
 // keys, 25 at 8000, 32 at 10000 and 47 at 16000, against 51, 61 and 64 with tiles of 4096 as

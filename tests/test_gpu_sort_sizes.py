@@ -1,5 +1,5 @@
 """The radix sort at the sizes where its route changes (one workgroup up to 8192 keys, tiles of
-1024 up to 2^18, tiles of 4096 above) and at its tiles' ends, for both key widths and every
+1024 up to 245760, tiles of 4096 above) and at its tiles' ends, for both key widths and every
 number of passes, against numpy's stable order."""
 import numpy as np
 import pytest
@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("wide", [False, True])
 @pytest.mark.parametrize("n", [2, 63, 64, 65, 1023, 1024, 1025, 4095, 4096, 4097, 8191, 8192, 8193,
-                               9216, 262143, 262144, 262145])
+                               9216, 245759, 245760, 245761, 262144, 262145])
 def test_sizes_about_the_routes(torch, n, wide):  # noqa: F811
     rng = np.random.default_rng(n)
     keys = rng.integers(0, 1 << 20, n, dtype=np.uint64)  # many ties: the order has to be stable
