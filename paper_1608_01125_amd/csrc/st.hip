@@ -297,6 +297,9 @@ __device__ __forceinline__ bool st_overlap(const float q[6], float4 lo, float4 h
 constexpr int kStQueries = 8;   // query photons of one wave
 constexpr int kStStack = 1024;  // pending nodes of a wave
 constexpr int kStDepth = 128;   // deeper than any radix tree over (key, index) pairs
+// Waves of one launch: a grid holds at most 2^32 - 1 threads, and eight per query and window
+// pass that from 2^29 queries times windows (the windows of one build times the query beam).
+constexpr int64_t kStLaunch = (int64_t)1 << 25;
 
 // Cloud traversal: one wave per kStQueries neighbouring query photons (in Morton order) and
 // window of win consecutive steps. The boxes hold the clouds swept over the window, so one
@@ -322,7 +325,7 @@ constexpr int kStDepth = 128;   // deeper than any radix tree over (key, index) 
 __global__ void __launch_bounds__(64, 4) k_st_traverse(
     const Node *__restrict__ nodes, int32_t n_int, const PBox *__restrict__ root_box,
     const PBox *__restrict__ qbox, const uint32_t *__restrict__ qorder, int64_t nq, int64_t groups,
-    const int32_t *__restrict__ inst_root, int64_t n_t, const StRec *__restrict__ qrec,
+    int64_t first, const int32_t *__restrict__ inst_root, int64_t n_t, const StRec *__restrict__ qrec,
     const StRec *__restrict__ trec, int64_t n_t_bins, double dt, int32_t win, int32_t k_begin,
     int32_t k_last, StCell cell, int mode, const long long *__restrict__ filter, uint64_t fmask,
     long long *keys, double *vals, uint64_t mask, double *__restrict__ slots, DevCounters *c) {
@@ -331,8 +334,9 @@ __global__ void __launch_bounds__(64, 4) k_st_traverse(
     __shared__ uint8_t s_owner[192];         //               and query lane
     __shared__ int32_t s_row[kStQueries];
     const int lane = threadIdx.x, ql = lane & (kStQueries - 1), grp = lane / kStQueries;
-    const int64_t so = blockIdx.x / groups;  // window of the launch
-    const int64_t qi = (blockIdx.x - so * groups) * kStQueries + ql;
+    const int64_t wave = first + blockIdx.x;
+    const int64_t so = wave / groups;  // window of the hierarchy
+    const int64_t qi = (wave - so * groups) * kStQueries + ql;
     int32_t root = -1, tag = -1;
     float qb[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     if (qi < nq) {
@@ -1158,12 +1162,13 @@ void launch_st_traverse(const Node *nodes, int64_t n_int64, const PBox *root_box
                         int64_t filter_cap, long long *keys, double *vals, int64_t cap,
                         double *slots, DevCounters *c, hipStream_t st) {
     if (nq <= 0 || m <= 0 || n_int64 < 0) return;
-    const int64_t groups = (nq + kStQueries - 1) / kStQueries;
-    hipLaunchKernelGGL(k_st_traverse, dim3((unsigned)(groups * m)), dim3(64), 0, st, nodes,
-                       (int32_t)n_int64, root_box, qbox, qorder, nq, groups, inst_root, n_t, qrec,
-                       trec, n_t_bins, dt, win, k_begin, k_last, cell, mode, filter,
-                       (uint64_t)(filter ? filter_cap - 1 : 0), keys, vals, (uint64_t)(cap - 1),
-                       slots, c);
+    const int64_t groups = (nq + kStQueries - 1) / kStQueries, waves = groups * m;
+    for (int64_t first = 0; first < waves; first += kStLaunch)
+        hipLaunchKernelGGL(k_st_traverse, dim3((unsigned)std::min(waves - first, kStLaunch)),
+                           dim3(64), 0, st, nodes, (int32_t)n_int64, root_box, qbox, qorder, nq,
+                           groups, first, inst_root, n_t, qrec, trec, n_t_bins, dt, win, k_begin,
+                           k_last, cell, mode, filter, (uint64_t)(filter ? filter_cap - 1 : 0),
+                           keys, vals, (uint64_t)(cap - 1), slots, c);
 }
 
 }  // namespace tril
