@@ -1680,10 +1680,15 @@ int st_run(tril_ctx *c, const tril_beam *t, const int32_t *t_bins, int64_t n_t_b
         if ((rc = enqueue_build(c, c->st, false)) != TRIL_OK) break;
         launch_prologue(c->d_cnt, 1, c->box_steps, c->st);
         if ((rc = enqueue_query_prep(c, qv, c->st, true)) != TRIL_OK) break;
-        launch_st_traverse(c->nodes, c->n_int, c->root_box, c->q_box, c->q_order, q->n, mb,
-                           c->inst_root, t->n, c->st_qrec, c->st_trec, n_t_bins, c->dt, win, k0,
-                           k0 + n_steps - 1, sc, mode, filter, filter_cap, keys, vals, cap,
-                           c->st_slots, c->d_cnt, c->st);
+        if (mode == 3)
+            launch_st_meet(c->nodes, c->n_int, c->root_box, c->q_box, c->q_order, q->n, mb,
+                           c->inst_root, t->n, c->st_qrec, c->st_trec, keys, vals, cap, c->d_cnt,
+                           c->st);
+        else
+            launch_st_traverse(c->nodes, c->n_int, c->root_box, c->q_box, c->q_order, q->n, mb,
+                               c->inst_root, t->n, c->st_qrec, c->st_trec, n_t_bins, c->dt, win, k0,
+                               k0 + n_steps - 1, sc, mode, filter, filter_cap, keys, vals, cap,
+                               c->st_slots, c->d_cnt, c->st);
         kw += mb;
         left -= mb;
     }

@@ -185,7 +185,7 @@ __global__ void __launch_bounds__(256) k_st_pack(BeamDev b, const int32_t *__res
 }
 
 // What the cloud traversal adds per overlapping pair and step.
-enum : int { kStYield = 0, kStOverlap = 1, kStExposure = 2, kStMeet = 3 };
+enum : int { kStYield = 0, kStOverlap = 1, kStExposure = 2 };
 
 // First and last step (clamped to [k0, k1]) in which two clouds at distance d + t v (per
 // axis, t the mid-step time) can overlap along one axis of edge c; sl is far above the FP64
@@ -232,18 +232,13 @@ __device__ __forceinline__ long long st_pair(const StRec &q, int64_t i, int32_t 
     cnt = 0;
     const StRec t = trec[j];
     if (t.bin < 0) return -1ll;
-    // bin-pair key, or in exposure and swarm mode the cloud pair (caller rows)
-    const long long key = mode >= kStExposure ? (long long)i * n_t + j
+    // bin-pair key, or in exposure mode the cloud pair (caller rows)
+    const long long key = mode == kStExposure ? (long long)i * n_t + j
                                               : (long long)q.bin * n_t_bins + t.bin;
     if (filter != nullptr && !set_has(filter, fmask, key)) return -1ll;
     const double cphi = (q.u[0] * t.u[0] + q.u[1] * t.u[1]) + q.u[2] * t.u[2];
     const double s = ((q.E * t.E) * (1.0 - cphi)) / (2.0 * kMe * kMe);
     if (!(s > 1.0)) return -1ll;
-    if (mode == kStMeet) {  // swarms: the swept clouds meet, above threshold
-        sum = 1.0;
-        cnt = 1;
-        return key;
-    }
     const double t_end = ((double)k1 + 1.0) * dt;
     double lo = (double)k0, hi = (double)k1;
 #pragma unroll
@@ -501,6 +496,94 @@ __global__ void __launch_bounds__(64, 4) k_st_traverse(
         if (v) atomicAdd(&c->visits[slot], v);
         if (np_) atomicAdd(&c->st_pairs[slot], np_);
         if (total != 0.0) atomicAdd(&slots[slot], total);
+    }
+}
+
+// Swarms: cloud pairs above threshold whose boxes, swept over one step, meet, each a key of the
+// table (its value counts the steps). One lane per query and step descends by itself, one load
+// per overlapped internal node, both children tested from it, pending right children on the
+// lane's stack. Most of these descents end after a few nodes without a leaf, so there is little
+// that neighbours could share, and a wave per kStQueries queries (k_st_traverse) pays its
+// latency for eight lanes' work: 3e4 macro-particles per beam over 400 steps 7.7 ms that way,
+// 0.8 ms so.
+__global__ void __launch_bounds__(256) k_st_meet(
+    const Node *__restrict__ nodes, int32_t n_int, const PBox *__restrict__ root_box,
+    const PBox *__restrict__ qbox, const uint32_t *__restrict__ qorder, int64_t nq, int64_t m,
+    const int32_t *__restrict__ inst_root, int64_t n_t, const StRec *__restrict__ qrec,
+    const StRec *__restrict__ trec, long long *keys, double *vals, uint64_t mask, DevCounters *c) {
+    const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    const int64_t so = e / nq;  // step of the launch
+    int64_t i = 0;
+    int32_t node = -1, tag = -1;
+    float qb[6] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    if (so < m) {
+        i = qorder[e - so * nq];
+        const float4 *bp = reinterpret_cast<const float4 *>(qbox + so * nq + i);
+        const float4 a = bp[0], b = bp[1];
+        qb[0] = a.x; qb[1] = a.y; qb[2] = a.z;
+        qb[3] = b.x; qb[4] = b.y; qb[5] = b.z;
+        tag = __float_as_int(a.w);
+        if (tag >= 0 && qrec[i].bin >= 0) node = inst_root[tag];
+    }
+    uint32_t visits = 0, n_pairs = 0;
+    auto leaf = [&](int32_t link) {
+        const int64_t j = link_elem(link) - so * n_t;
+        const StRec &q = qrec[i], &t = trec[j];
+        if (t.bin < 0) return;
+        const double cphi = (q.u[0] * t.u[0] + q.u[1] * t.u[1]) + q.u[2] * t.u[2];
+        const double s = ((q.E * t.E) * (1.0 - cphi)) / (2.0 * kMe * kMe);
+        if (!(s > 1.0)) return;
+        ++n_pairs;
+        table_add(keys, vals, mask, i * n_t + j, 1.0, &c->err);
+    };
+    if (node <= -2) {  // an instance of one row: its root is that leaf
+        const float4 *lp = reinterpret_cast<const float4 *>(root_box + tag);
+        ++visits;
+        if (st_overlap(qb, lp[0], lp[1])) leaf(node);
+        node = -1;
+    }
+    int32_t stack[kStDepth];
+    int32_t depth = 0;
+    const uint32_t max_visits = (uint32_t)n_int + 2u;
+    while (node >= 0) {
+        if (visits > max_visits) {
+            atomicOr(&c->err, kErrSpin);
+            break;
+        }
+        const float4 *np = reinterpret_cast<const float4 *>(nodes + node);
+        const float4 l0 = np[0], l1 = np[1], r0 = np[2], r1 = np[3];
+        ++visits;
+        const int32_t lc = __float_as_int(l0.w), rc = __float_as_int(r0.w);
+        const bool ovl = st_overlap(qb, l0, l1), ovr = st_overlap(qb, r0, r1);
+        if (ovl && lc < 0) leaf(lc);
+        if (ovr && rc < 0) leaf(rc);
+        const bool gol = ovl && lc >= 0, gor = ovr && rc >= 0;
+        if (gol) {
+            if (gor) {
+                if (depth >= kStDepth) {
+                    atomicOr(&c->err, kErrSpin);
+                    break;
+                }
+                stack[depth++] = rc;
+            }
+            node = lc;
+        } else if (gor) {
+            node = rc;
+        } else {
+            node = depth > 0 ? stack[--depth] : -1;
+        }
+    }
+    // per-wave sums into spread slots
+    unsigned long long v = visits, np_ = n_pairs;
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        v += __shfl_xor(v, off);
+        np_ += __shfl_xor(np_, off);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        const int slot = blockIdx.x & (kCounterSlots - 1);
+        if (v) atomicAdd(&c->visits[slot], v);
+        if (np_) atomicAdd(&c->st_pairs[slot], np_);
     }
 }
 
@@ -1169,6 +1252,16 @@ void launch_st_traverse(const Node *nodes, int64_t n_int64, const PBox *root_box
                            groups, first, inst_root, n_t, qrec, trec, n_t_bins, dt, win, k_begin,
                            k_last, cell, mode, filter, (uint64_t)(filter ? filter_cap - 1 : 0),
                            keys, vals, (uint64_t)(cap - 1), slots, c);
+}
+
+void launch_st_meet(const Node *nodes, int64_t n_int, const PBox *root_box, const PBox *qbox,
+                    const uint32_t *qorder, int64_t nq, int32_t m, const int32_t *inst_root,
+                    int64_t n_t, const StRec *qrec, const StRec *trec, long long *keys, double *vals,
+                    int64_t cap, DevCounters *c, hipStream_t st) {
+    if (nq <= 0 || m <= 0 || n_int < 0) return;
+    hipLaunchKernelGGL(k_st_meet, dim3(grid_for(nq * m, 256)), dim3(256), 0, st, nodes,
+                       (int32_t)n_int, root_box, qbox, qorder, nq, (int64_t)m, inst_root, n_t, qrec,
+                       trec, keys, vals, (uint64_t)(cap - 1), c);
 }
 
 }  // namespace tril
