@@ -245,7 +245,9 @@ struct tril_ctx {
     uint8_t *dead_q = nullptr, *dead_t = nullptr;  // photons consumed in this run (per row)
     int64_t dead_cap_q = 0, dead_cap_t = 0;
     int64_t *ann_count = nullptr;                  // kept hits of one batch (device)
-    unsigned long long *swarm_total = nullptr;  // IP regime: colliding real pairs
+    unsigned long long *swarm_total = nullptr;  // IP regime: colliding real pairs, pairs listed
+    uint32_t *swarm_list = nullptr;             // occupied slots of a piece of the pair table
+    int64_t swarm_list_cap = 0;
     GridDev *grid_dev = nullptr;    // uniform-grid broad phase (TRIL_GRID)
     int32_t *grid_start = nullptr, *grid_end = nullptr;
     int64_t grid_cap = 0;
@@ -2098,18 +2100,25 @@ int tril_ip_swarm(tril_ctx *c, const tril_beam *t, const int32_t *t_bins, int64_
     if (q->n_inst != t->n_inst) return TRIL_E_STATE;
     if ((int64_t)k0 + n_steps - 1 > INT32_MAX) return TRIL_E_INVAL;
     *total = 0;
-    if (!c->swarm_total) CHK(dev_alloc(&c->swarm_total, 1));
+    if (!c->swarm_total) CHK(dev_alloc(&c->swarm_total, 2));
+    const int64_t list = std::min(pair_tab->cap, kSwarmList);
+    if (list > c->swarm_list_cap) {
+        dev_free(c->swarm_list);
+        c->swarm_list_cap = 0;
+        CHK(dev_alloc(&c->swarm_list, (size_t)list));
+        c->swarm_list_cap = list;
+    }
     long long *pkeys = reinterpret_cast<long long *>(pair_tab->key);
     CHK(st_run(c, t, t_bins, n_t_bins, q, q_bins, cell, k0, n_steps, 3, nullptr, 0, pkeys,
                pair_tab->yield, pair_tab->cap));
     long long *keys = reinterpret_cast<long long *>(tab->key);
     launch_st_clear(keys, tab->yield, tab->cap, c->st_slots, c->st);
-    HIPCHK(hipMemsetAsync(c->swarm_total, 0, sizeof(unsigned long long), c->st));
+    HIPCHK(hipMemsetAsync(c->swarm_total, 0, 2 * sizeof(unsigned long long), c->st));
     const StCell sc{{cell[0], cell[1], cell[2]}};
     launch_swarm(pkeys, pair_tab->yield, pair_tab->cap, view(q, c->d_q_off, 1),
                  view(t, c->d_t_off, 1), q_bins, t_bins, n_t_bins, sc, (double)k0 * c->dt,
-                 (double)n_steps * c->dt, keys, tab->yield, tab->cap, c->swarm_total, c->d_cnt,
-                 c->st);
+                 (double)n_steps * c->dt, keys, tab->yield, tab->cap, c->swarm_list, c->swarm_total,
+                 c->d_cnt, c->st);
     HIPCHK(hipGetLastError());
     CHK(st_finish(c, nullptr));
     unsigned long long tot = 0;
@@ -2811,6 +2820,7 @@ void tril_destroy(tril_ctx *c) {
     dev_free(c->kin_buf);
     dev_free(c->kin_rec);
     dev_free(c->swarm_total);
+    dev_free(c->swarm_list);
     dev_free(c->grid_dev);
     dev_free(c->grid_start);
     dev_free(c->grid_end);

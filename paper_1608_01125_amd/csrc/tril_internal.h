@@ -651,12 +651,14 @@ void launch_st_deplete(long long *pkeys, double *pvals, int64_t pcap, const Beam
                        int64_t cap, double *slots, DevCounters *c, hipStream_t st);
 // IP-regime swarms over the macro-particle pairs of the pair table (pkeys = i * t.n + j):
 // colliding real-photon pairs of each pair over the window [T0, T0 + Tw] into pvals (as
-// doubles), into the bin-pair table under (q_bins[i], t_bins[j]) and into *total.
+// doubles), into the bin-pair table under (q_bins[i], t_bins[j]) and into *total. total: two
+// words, zero; list: room for min(pcap, kSwarmList) slots (larger tables go in pieces of those).
+constexpr int64_t kSwarmList = (int64_t)1 << 24;
 void launch_swarm(const long long *pkeys, double *pvals, int64_t pcap, const BeamDev &q,
                   const BeamDev &t, const int32_t *q_bins, const int32_t *t_bins,
                   int64_t n_t_bins, const StCell &cell, double T0, double Tw, long long *keys,
-                  double *vals, int64_t cap, unsigned long long *total, DevCounters *c,
-                  hipStream_t st);
+                  double *vals, int64_t cap, uint32_t *list, unsigned long long *total,
+                  DevCounters *c, hipStream_t st);
 // Photons as the cloud traversal reads them (one record per caller row).
 struct alignas(16) StRec {
     double x[3], u[3];  // position at t = 0, direction p / E

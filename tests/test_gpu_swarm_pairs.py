@@ -7,7 +7,7 @@ import pytest
 
 from paper_1608_01125_amd import tril as T
 
-from test_gpu_swarm import ME, torch  # noqa: F401
+from test_gpu_swarm import ME, _check, _tiny, torch  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 CELL, DT, K0, STEPS, MARGIN = (0.4, 0.6, 0.5), 0.25, 3, 37, 1e-5
@@ -74,3 +74,17 @@ def test_pairs_whose_swept_clouds_meet(torch, sizes, step_batch):  # noqa: F811
     if sizes != ((40, 5), (0, 1)):
         assert sure
     assert sure <= got <= may
+
+
+@pytest.mark.parametrize("pair_log2", [0, 5, 6, 9, 25])
+def test_pairs_are_found_in_tables_of_any_size(torch, pair_log2):  # noqa: F811
+    """The table's pairs are listed before they are counted, those of one block of 64 photons
+    apart from the others, and tables above 2^24 slots in pieces: one pair in one slot, full
+    words, and two pieces."""
+    n = 1 if pair_log2 == 0 else 6
+    A, B = _tiny(31, n, along=1e-3, spread=1e-9)
+    A["w"] = np.resize([64.0, 65.0, 1.0, 600.0, 63.0, 513.0], n)
+    B["w"] = np.resize([500.0, 3.0, 64.0, 65.0, 1.0], n)
+    if pair_log2 == 5:  # 30 pairs of 32 slots
+        B = {f: v[:5] for f, v in B.items()}
+    _check(torch, A, B, (4e-9,) * 3, pair_log2=pair_log2)
