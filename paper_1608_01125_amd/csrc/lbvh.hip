@@ -740,16 +740,17 @@ __global__ void k_win_bounds(const InstStats *__restrict__ stats, int32_t n_inst
 // Quantisation frame of every window copy: the union over instances of where the
 // photons can be during the copy's step (positions at t = 0 and directions bounded by the
 // statistics; x0 + u t over the step's time window is extremal at the corners), widened by
-// a margin eight times the rounding of the FP32 leaf boxes (below 2^-19 (|x| + m dt)).
-__global__ void k_win_frames(const InstStats *__restrict__ stats, int32_t n_inst, double dt,
+// a margin eight times the rounding of the FP32 leaf boxes (below 2^-19 (|x| + m dt)). A wave
+// per copy, its lanes striding the instances (minima and maxima, the same in any order): one
+// lane took 418 us per launch for 500 instances.
+__global__ void __launch_bounds__(64) k_win_frames(const InstStats *__restrict__ stats, int32_t n_inst, double dt,
                              int32_t win, int32_t m, const DevCounters *__restrict__ c,
                              const WinBound *__restrict__ vb, WinFrame *__restrict__ frames) {
-    const int32_t cp = blockIdx.x * blockDim.x + threadIdx.x;
-    if (cp >= window_copies(m, win)) return;
+    const int32_t cp = blockIdx.x;
     const int32_t r = window_ref_step(cp, win, m);
     const double t0 = (double)(c->step + (unsigned)r) * dt, t1 = t0 + dt;
     double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-    for (int32_t mi = 0; mi < n_inst; ++mi) {
+    for (int32_t mi = threadIdx.x; mi < n_inst; mi += 64) {
         const InstStats &st = stats[mi];
         if (st.mn[0] > st.mx[0]) continue;  // no usable photon
         double il[3], ih[3];
@@ -781,6 +782,13 @@ __global__ void k_win_frames(const InstStats *__restrict__ stats, int32_t n_inst
             hi[a] = fmax(hi[a], ih[a] + mg);
         }
     }
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+        for (int off = 32; off >= 1 && n_inst > 1; off >>= 1) {
+            lo[a] = fmin(lo[a], __shfl_xor(lo[a], off));
+            hi[a] = fmax(hi[a], __shfl_xor(hi[a], off));
+        }
+    if (threadIdx.x != 0) return;
     float base[3], inv[3];
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
@@ -1572,7 +1580,7 @@ void launch_win_frames(const InstStats *stats, int32_t n_inst, double dt, int32_
                        const DevCounters *c, const WinBound *vb, WinFrame *frames, hipStream_t st) {
     const int32_t nc = window_copies(m, win);
     if (nc <= 0) return;
-    hipLaunchKernelGGL(k_win_frames, dim3(grid_for(nc, 64)), dim3(64), 0, st, stats, n_inst, dt,
+    hipLaunchKernelGGL(k_win_frames, dim3((unsigned)nc), dim3(64), 0, st, stats, n_inst, dt,
                        win, m, c, vb, frames);
 }
 
