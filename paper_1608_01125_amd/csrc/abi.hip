@@ -80,8 +80,14 @@ constexpr int64_t kBatchStepsMin = 32;
 // pairs that never overlap and leave fewer waves. Training rows of 2e4 clouds per beam and the
 // audit of 2e5, 16 queries per wave: 17.4 and 43.8 ms at 4 steps, 13.0 and 32.4 at 8, 11.0 and
 // 26.8 at 16, 11.3 and 27.9 at 32, 12.6 and 29.3 at 64; with 8 queries per wave, as now, 8.93 and
-// 22.1 at 16, 8.69 and 21.7 at 32.
+// 22.1 at 16, 8.69 and 21.7 at 32. These are steps of a fifth of the cloud's shortest edge. The
+// boxes of clouds that cross at an angle grow with the square of the window's length, the pairs
+// that overlap only with the length, so a window is no longer than kStWinEdges such edges: 1e5
+// clouds per beam at 90 degrees take 55.3 ms per pass with steps of 4 edges in windows of 32, 6.8
+// step by step; steps of one edge 43.1 ms in windows of 32, 20.8 of 8 and 16.5 of 4 (head-on
+// beams 12.4, 13.0 and 15.0 ms).
 constexpr int64_t kStWin = 32;
+constexpr double kStWinEdges = 6.5;
 // with window copies (the plain regime) a launch's tree buffers hold a copy per window, not
 // per step, and its query buffers one record per row: every beam takes up to kBatchBudgetMax
 // virtual elements per launch (the whole 400-step run of two 1e6-photon beams in one launch,
@@ -125,7 +131,7 @@ struct tril_ctx {
     int64_t ad_checks0 = 0, ad_queries0 = 0;
     bool ad_quad = false;           // a tril_run since then descended four-child forms
     int morton_param = 0;           // Morton bits requested (0 = automatic)
-    CloudBox cloud{0, {0.0, 0.0, 0.0}};  // box kind of the builds (statistical regime: clouds)
+    CloudBox cloud{0, {0.0, 0.0, 0.0}, 0.0};  // box kind of the builds (statistical regime: clouds)
     double box_dt = 0.0;            // time one box covers: dt, or a window of the statistical
     int32_t box_steps = 0;          // regime; the steps its launch covers (0: one per box)
     double *st_slots = nullptr;     // statistical regime: per-wave yield sums (kCounterSlots)
@@ -212,7 +218,7 @@ struct tril_ctx {
     int64_t refit_slot_cap = 0;
     int64_t n_int = -1;                    // internal nodes of the last build (all steps)
     int32_t tgt_k0 = 0;                    // first step of the last build
-    CloudBox tgt_cloud{0, {0.0, 0.0, 0.0}};  // box kind of the last build
+    CloudBox tgt_cloud{0, {0.0, 0.0, 0.0}, 0.0};  // box kind of the last build
     double tgt_dt = 0.0;                     // time one box of the last build covers
 
     // query state
@@ -1643,8 +1649,10 @@ int st_run(tril_ctx *c, const tril_beam *t, const int32_t *t_bins, int64_t n_t_b
     const int32_t ms = n_steps > 0 ? pick_batch(c, t, q, n_steps) : 1;
     // swarms (mode 3) keep a descent per step: their pairs are those whose clouds, swept over
     // one step, meet
+    const double edge = std::min(cell[0], std::min(cell[1], cell[2]));
+    const int64_t longest = (int64_t)std::min((double)kStWin, kStWinEdges * edge / c->dt);
     const int32_t win =
-        mode == 3 ? 1 : (int32_t)std::max<int64_t>(1, std::min<int64_t>(kStWin, std::min(n_steps, ms)));
+        mode == 3 ? 1 : (int32_t)std::max<int64_t>(1, std::min<int64_t>(longest, std::min(n_steps, ms)));
     // windows are aligned to multiples of their length; the first and the last may be cut
     const int64_t kw0 = k0 / win;
     const int64_t n_win = n_steps > 0 ? (k0 + (int64_t)n_steps - 1) / win - kw0 + 1 : 0;
@@ -1665,8 +1673,8 @@ int st_run(tril_ctx *c, const tril_beam *t, const int32_t *t_bins, int64_t n_t_b
     launch_st_pack(t1, t_bins, c->st_trec, c->st);
     launch_st_pack(q1, q_bins, c->st_qrec, c->st);
     const StCell sc{{cell[0], cell[1], cell[2]}};
-    // clouds swept over a window (swarms: over a step)
-    c->cloud = CloudBox{1, {0.5 * cell[0], 0.5 * cell[1], 0.5 * cell[2]}};
+    // clouds swept from a window's first mid-step to its last (swarms: over a step)
+    c->cloud = CloudBox{1, {0.5 * cell[0], 0.5 * cell[1], 0.5 * cell[2]}, mode == 3 ? 0.0 : 0.5 * c->dt};
     c->box_dt = (double)win * c->dt;
     c->morton_bits = c->morton_param > 0 ? c->morton_param : 30;
     int rc = TRIL_OK;

@@ -321,11 +321,10 @@ __device__ __forceinline__ RowPhoton load_photon(const BeamDev &b, int64_t i, do
 
 // Box of photon r in the step window [t, t + dt], padded by pad and rounded outward to
 // FP32, and its centre: the swept segment (position at t exactly as the narrow phase
-// forms it, and one step later); in the statistical regime (cloud.on) the cloud swept over
-// the window (the segment's box widened by the cloud's half-widths cloud.h), which holds the
-// cloud of every mid-step in it: those lie half a step inside the segment's ends, and where
-// a photon hardly moves along an axis the slack below covers the rounding of its positions.
-// A photon with unusable data gets an empty box.
+// forms it, and one step later); in the statistical regime (cloud.on) the cloud (half-widths
+// cloud.h) swept over [t + inset, t + dt - inset], from the window's first mid-step to its last
+// (inset half a step; the slack below covers the rounding of the positions), or, for swarms,
+// over the whole step (inset 0). A photon with unusable data gets an empty box.
 __device__ __forceinline__ void photon_box(const RowPhoton &r, double t, double dt,
                                            const CloudBox &cloud, double pad, float lo32[3],
                                            float hi32[3], float cen[3]) {
@@ -337,6 +336,10 @@ __device__ __forceinline__ void photon_box(const RowPhoton &r, double t, double 
             cen[a] = 0.0f;
         }
         return;
+    }
+    if (cloud.on) {
+        t += cloud.inset;
+        dt -= 2.0 * cloud.inset;
     }
     double lo[3], hi[3];
     const double ax = r.x + t * r.ux, ay = r.y + t * r.uy, az = r.z + t * r.uz;

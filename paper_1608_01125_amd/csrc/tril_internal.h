@@ -380,10 +380,12 @@ void launch_beam_stats(const BeamDev &b, StatsPartial *partials, InstStats *stat
 // virtual element index). Morton quantisation bounds come from self_stats; query
 // padding and the threshold prune from t_stats (target instance statistics).
 // Box kind for launch_boxes_keys: the swept segment of a step (on = 0), or the cloud of
-// the statistical regime swept over a window (on = 1): the segment widened by h per axis.
+// the statistical regime swept over a window, but for inset at each end (on = 1): the segment
+// widened by h per axis.
 struct CloudBox {
     int on;
     double h[3];
+    double inset;
 };
 
 // Boxes of all b.m steps at s b.n + i; sort keys (key layout kl, base-instance prefix)

@@ -48,3 +48,25 @@ def test_more_waves_than_a_grid_holds(torch):  # noqa: F811
                 meet.append((at, int(i) * TARGETS + j))
     assert len(meet) > 20 and min(meet)[0] < 15.0 and max(meet)[0] > 35.0
     assert {k for _, k in meet} <= set(found[0][0].tolist())
+
+
+def test_more_waves_of_fast_clouds(torch):  # noqa: F811
+    """The same of the cloud traversal, steps of eight cells (windows of one step)."""
+    A, B = _beam(N, 3, 50.0, 1.0), _beam(TARGETS, 4, 49.0, -1.0)
+    for b in (A, B):
+        b["z"] *= 4.0
+    qa, tb = T.Beam(A), T.Beam(B)
+    qbins = torch.arange(N, dtype=torch.int32, device="cuda")
+    tbins = torch.arange(TARGETS, dtype=torch.int32, device="cuda")
+    found = []
+    for step_batch in (0, 64):
+        ctx, tab = T.Context(4 * DT, None, step_batch=step_batch), T.StTable(12)
+        try:
+            tot = T.tril_st_exact(ctx, tb, tbins, TARGETS, qa, qbins, CELL, 0, STEPS, tab)
+        finally:
+            ctx.close()
+        found.append((*tab.items(), tot))
+    assert len(found[0][0]) > 2 and np.array_equal(found[0][0], found[1][0])
+    # a key's value is one sum over a pair's steps, the total one over all of them
+    np.testing.assert_allclose(found[0][1], found[1][1], rtol=1e-14, atol=0)
+    assert found[0][2] == pytest.approx(found[1][2], rel=1e-12)
