@@ -207,7 +207,8 @@ int tril_build(tril_ctx *ctx, const tril_beam *target, int32_t step);
 /* Query the last built hierarchy with every photon of `query` at the same step
  * and append the hits to `out`. `query` must have the same n_inst as the target
  * (instance m of the query meets instance m of the target). TRIL_E_STATE if no
- * hierarchy was built or the step differs from the build's step. */
+ * hierarchy was built, the step differs from the build's step, or a call of the statistical
+ * regime has come since (its hierarchies are of clouds over windows of steps). */
 int tril_collide(tril_ctx *ctx, const tril_beam *query, int32_t step, tril_pairs *out);
 
 /* Build + collide for steps k0 .. k0+n_steps-1 in one call; the result is the same

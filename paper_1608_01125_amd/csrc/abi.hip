@@ -740,6 +740,8 @@ int enqueue_grid_build(tril_ctx *c, hipStream_t st, bool timed) {
                       c->t_k32a, c->t_va, c->grid_start, c->grid_end, st);
     const uint32_t *keys = c->t_k32a;
     c->t_rows = c->t_va;
+    c->tgt_cloud = c->cloud;
+    c->tgt_dt = c->dt;
     if (n > 1) {
         const bool alt = radix_sort_u32(c->t_k32a, c->t_va, c->t_k32b, c->t_vb, n,
                                         std::max(1, bits_for((uint64_t)(max_cells - 1))), c->ss,
@@ -1141,7 +1143,9 @@ int tril_collide(tril_ctx *c, const tril_beam *q, int32_t step, tril_pairs *out)
     if (!c) return TRIL_E_INVAL;
     CHK(check_beam(q));
     CHK(check_pairs(out));
-    if (!c->built || c->tgt.m != 1 || step != c->built_step || q->n_inst != c->tgt.n_inst)
+    // (a statistical pass leaves clouds of its windows, not a step's photons)
+    if (!c->built || c->tgt_cloud.on != 0 || c->tgt.m != 1 || step != c->built_step ||
+        q->n_inst != c->tgt.n_inst)
         return TRIL_E_STATE;
     c->morton_bits = c->morton_param > 0 ? c->morton_param : 30;
     CHK(ensure_query(c, q->n, q->n, q->n_inst, q->n_inst));
@@ -1708,7 +1712,7 @@ int st_run(tril_ctx *c, const tril_beam *t, const int32_t *t_bins, int64_t n_t_b
     CHK(rc);
     HIPCHK(hipGetLastError());
     c->built = true;
-    c->built_step = k0 + std::max(n_steps, 1) - 1;
+    c->built_step = n_steps > 0 ? k0 + n_steps - 1 : -1;  // without steps there is no hierarchy
     c->res_t = t1;
     c->last_q = q1;
     return TRIL_OK;
