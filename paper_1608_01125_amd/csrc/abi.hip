@@ -217,7 +217,7 @@ struct tril_ctx {
     int32_t *xlev = nullptr;               // crossing levels of the shape (batches of many steps)
     int64_t refit_slot_cap = 0;
     int64_t n_int = -1;                    // internal nodes of the last build (all steps)
-    int32_t tgt_k0 = 0;                    // first step of the last build
+    int32_t tgt_k0 = 0;                    // first box of the last build, at tgt_k0 tgt_dt
     CloudBox tgt_cloud{0, {0.0, 0.0, 0.0}, 0.0};  // box kind of the last build
     double tgt_dt = 0.0;                     // time one box of the last build covers
 
@@ -1690,7 +1690,7 @@ int st_run(tril_ctx *c, const tril_beam *t, const int32_t *t_bins, int64_t n_t_b
         c->tgt = view(t, c->d_t_off, mb);
         const BeamDev qv = view(q, c->d_q_off, mb);
         launch_set_step(c->d_cnt, (int32_t)kw, c->st);
-        c->tgt_k0 = (int32_t)ka;
+        c->tgt_k0 = (int32_t)kw;  // in boxes of tgt_dt
         if ((rc = enqueue_build(c, c->st, false)) != TRIL_OK) break;
         launch_prologue(c->d_cnt, 1, c->box_steps, c->st);
         if ((rc = enqueue_query_prep(c, qv, c->st, true)) != TRIL_OK) break;

@@ -1,5 +1,6 @@
 """What a statistical pass leaves in the context: its hierarchies are of clouds over windows of
 steps, which tril_collide does not take for a step's build, whatever their number."""
+import numpy as np
 import pytest
 
 from paper_1608_01125_amd import beams
@@ -58,3 +59,28 @@ def test_collide_needs_a_build_of_its_own(torch, k0, n_steps, flags):  # noqa: F
             assert want
     finally:
         ctx.close()
+
+
+@pytest.mark.parametrize("k0,n_steps", [(192, 32), (200, 1), (70, 20), (185, 40), (100, 100)])
+def test_boxes_of_a_pass_hold_its_clouds(torch, k0, n_steps):  # noqa: F811
+    """tril_dbg_boxes after a pass gives its last launch's windows, of 32 steps (or of the whole
+    pass, where that is shorter): the clouds of every mid-step, and no more than a step beyond."""
+    wl, ga, gb, ((qa, qbins), (tb, tbins)) = _setup(torch)
+    B = beams.draw_pair(wl)[1]
+    win = min(32, n_steps)
+    ctx = T.Context(wl.dt, None)
+    try:
+        T.tril_st_exact(ctx, tb, tbins, gb.n_bins, qa, qbins, ga.cell, k0, n_steps, T.StTable(18))
+        box = T.tril_dbg_boxes(ctx, 0, (n_steps // win) * N)
+    finally:
+        ctx.close()
+    windows = len(box["lo"]) // N
+    assert windows >= 1 and len(box["lo"]) == windows * N
+    for s in range(windows):
+        first = ((k0 + n_steps - 1) // win - windows + 1 + s) * win
+        rows = slice(s * N, (s + 1) * N)
+        for a, f in enumerate(("x", "y", "z")):
+            mid = [B[f] + (first + t + 0.5) * wl.dt * B["p" + f] / B["E"] for t in (0, win - 1)]
+            lo, hi = np.minimum(*mid) - 0.5 * ga.cell[a], np.maximum(*mid) + 0.5 * ga.cell[a]
+            assert (box["lo"][rows, a] <= lo).all() and (box["hi"][rows, a] >= hi).all()
+            assert (box["lo"][rows, a] > lo - wl.dt).all() and (box["hi"][rows, a] < hi + wl.dt).all()
