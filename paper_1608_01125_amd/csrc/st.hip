@@ -783,8 +783,11 @@ __global__ void __launch_bounds__(64 * kSwarmWaves, 4) k_swarm(
                 M += fabs(xi[a]) + fabs(xj[a]) + 2.0 * T0 + cell.c[a];
             }
             const double vv = (v[0] * v[0] + v[1] * v[1]) + v[2] * v[2];
-            const double vn = sqrt(vv), iv = 1.0 / vn;
-            const double w[3] = {v[0] * iv, v[1] * iv, v[2] * iv};
+            // two photons of one direction can be above threshold (|p| and E agree to 1e-12): no
+            // motion, every approach is cut off, and any axis will do
+            const bool still = !(vv > 1e-200);
+            const double vn = sqrt(vv), iv = still ? 0.0 : 1.0 / vn;
+            const double w[3] = {v[0] * iv, v[1] * iv, still ? 1.0 : v[2] * iv};
             // e1 across v and the axis v leans on least, e2 across both
             const double aw[3] = {fabs(w[0]), fabs(w[1]), fabs(w[2])};
             const int ax = aw[0] <= aw[1] ? (aw[0] <= aw[2] ? 0 : 2) : (aw[1] <= aw[2] ? 1 : 2);
