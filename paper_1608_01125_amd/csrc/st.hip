@@ -747,9 +747,7 @@ constexpr int kSwarmStack = 576;
 __global__ void __launch_bounds__(64 * kSwarmWaves, 4) k_swarm(
     const long long *__restrict__ pkeys, double *__restrict__ pvals, int64_t pcap,
     const uint32_t *__restrict__ list, const uint32_t *__restrict__ listed, BeamDev q, BeamDev t,
-    const int32_t *__restrict__ q_bins, const int32_t *__restrict__ t_bins,
-    int64_t n_t_bins, StCell cell, double T0, double Tw, long long *keys, double *vals,
-    uint64_t mask, unsigned long long *total, DevCounters *c) {
+    StCell cell, double T0, double Tw, DevCounters *c) {
     __shared__ uint2 s_node[kSwarmWaves][kSwarmStack];  // (octant digits, level)
     __shared__ double2 s_ab[kSwarmWaves][64];
     __shared__ unsigned long long s_part[kSwarmWaves];
@@ -934,15 +932,34 @@ __global__ void __launch_bounds__(64 * kSwarmWaves, 4) k_swarm(
         if (threadIdx.x == 0) {
             unsigned long long tot = 0;
             for (int k = 0; k < kSwarmWaves; ++k) tot += s_part[k];
-            if (tot) {  // whole numbers below 2^53: exact in any order
-                atomicAdd(&pvals[slot], (double)tot);
-                atomicAdd(total, tot);
-                table_add(keys, vals, mask, (long long)q_bins[i] * n_t_bins + t_bins[j],
-                          (double)tot, &c->err);
-            }
+            if (tot) atomicAdd(reinterpret_cast<unsigned long long *>(pvals) + slot, tot);
         }
         __syncthreads();
     }
+}
+
+// The listed pairs' counts, whole numbers so far (up to 2^60: a sum of doubles would depend on the
+// order above 2^53), as doubles, into the bin-pair table and into *total.
+__global__ void __launch_bounds__(256) k_swarm_bins(
+    const long long *__restrict__ pkeys, double *__restrict__ pvals, int64_t pcap,
+    const uint32_t *__restrict__ list, const uint32_t *__restrict__ listed, int64_t n_t,
+    const int32_t *__restrict__ q_bins, const int32_t *__restrict__ t_bins, int64_t n_t_bins,
+    long long *keys, double *vals, uint64_t mask, unsigned long long *total, DevCounters *c) {
+    const int64_t n_multi = listed[0], n = n_multi + listed[1];
+    unsigned long long sum = 0;
+    for (int64_t at = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; at < n;
+         at += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t slot = list[at < n_multi ? at : pcap - 1 - (at - n_multi)];
+        const unsigned long long tot = (unsigned long long)__double_as_longlong(pvals[slot]);
+        if (!tot) continue;
+        pvals[slot] = (double)tot;
+        sum += tot;
+        const int64_t i = pkeys[slot] / n_t, j = pkeys[slot] - i * n_t;
+        table_add(keys, vals, mask, (long long)q_bins[i] * n_t_bins + t_bins[j], (double)tot, &c->err);
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off);
+    if ((threadIdx.x & 63) == 0 && sum) atomicAdd(total, sum);
 }
 
 // One cloud per occupied bin: weighted-mean energy, direction and position (at the grid
@@ -1259,8 +1276,10 @@ void launch_swarm(const long long *pkeys, double *pvals, int64_t pcap, const Bea
                            pvals + a, n, q.w, t.n, list, listed);
         hipLaunchKernelGGL(k_swarm, dim3((unsigned)std::min<int64_t>(n, 16384), kSwarmSplit),
                            dim3(64 * kSwarmWaves), 0, st, pkeys + a, pvals + a, n, list, listed, q,
-                           t, q_bins, t_bins, n_t_bins, cell, T0, Tw, keys, vals,
-                           (uint64_t)(cap - 1), total, c);
+                           t, cell, T0, Tw, c);
+        hipLaunchKernelGGL(k_swarm_bins, dim3((unsigned)std::min<int64_t>(grid_for(n, 256), 512)),
+                           dim3(256), 0, st, pkeys + a, pvals + a, n, list, listed, t.n, q_bins,
+                           t_bins, n_t_bins, keys, vals, (uint64_t)(cap - 1), total, c);
     }
 }
 

@@ -7,7 +7,7 @@ import pytest
 
 from paper_1608_01125_amd import tril as T
 
-from test_gpu_swarm import ME, _check, _tiny, torch  # noqa: F401
+from test_gpu_swarm import ME, _check, _run, _tiny, torch  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 CELL, DT, K0, STEPS, MARGIN = (0.4, 0.6, 0.5), 0.25, 3, 37, 1e-5
@@ -88,3 +88,16 @@ def test_pairs_are_found_in_tables_of_any_size(torch, pair_log2):  # noqa: F811
     if pair_log2 == 5:  # 30 pairs of 32 slots
         B = {f: v[:5] for f, v in B.items()}
     _check(torch, A, B, (4e-9,) * 3, pair_log2=pair_log2)
+
+
+@pytest.mark.parametrize("ni,nj", [(132334651, 1073072517), (132334651, 1065067422), (70001, 65537)])
+def test_counts_of_the_largest_swarms(torch, ni, nj):  # noqa: F811
+    """Clouds far smaller than r that pass through each other: every real pair collides. The
+    pair's count is the whole number rounded once, also above 2^53, where a sum of its parts in
+    double precision rounds to a neighbour in any order (the first two)."""
+    A, B = _tiny(41, 1, spread=0.0, along=0.0)
+    A["w"][0], B["w"][0] = ni, nj
+    for _ in range(3):
+        tot, pk, pv, bk, bv = _run(torch, A, B, (1e-11,) * 3)
+        assert tot == ni * nj
+        assert pk.tolist() == bk.tolist() == [0] and pv[0] == bv[0] == float(ni * nj)
