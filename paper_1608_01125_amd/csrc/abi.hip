@@ -1696,8 +1696,8 @@ int st_run(tril_ctx *c, const tril_beam *t, const int32_t *t_bins, int64_t n_t_b
         if ((rc = enqueue_query_prep(c, qv, c->st, true)) != TRIL_OK) break;
         if (mode == 3)
             launch_st_meet(c->nodes, c->n_int, c->root_box, c->q_box, c->q_order, q->n, mb,
-                           c->inst_root, t->n, c->st_qrec, c->st_trec, keys, vals, cap, c->d_cnt,
-                           c->st);
+                           c->inst_root, t->n, c->st_qrec, c->st_trec, c->dt, k0,
+                           k0 + n_steps - 1, sc, keys, vals, cap, c->st_slots, c->d_cnt, c->st);
         else
             launch_st_traverse(c->nodes, c->n_int, c->root_box, c->q_box, c->q_order, q->n, mb,
                                c->inst_root, t->n, c->st_qrec, c->st_trec, n_t_bins, c->dt, win, k0,

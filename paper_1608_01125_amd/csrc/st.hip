@@ -185,7 +185,7 @@ __global__ void __launch_bounds__(256) k_st_pack(BeamDev b, const int32_t *__res
 }
 
 // What the cloud traversal adds per overlapping pair and step.
-enum : int { kStYield = 0, kStOverlap = 1, kStExposure = 2 };
+enum : int { kStYield = 0, kStOverlap = 1, kStExposure = 2, kStMeet = 3 };
 
 // First and last step (clamped to [k0, k1]) in which two clouds at distance d + t v (per
 // axis, t the mid-step time) can overlap along one axis of edge c; sl is far above the FP64
@@ -232,13 +232,18 @@ __device__ __forceinline__ long long st_pair(const StRec &q, int64_t i, int32_t 
     cnt = 0;
     const StRec t = trec[j];
     if (t.bin < 0) return -1ll;
-    // bin-pair key, or in exposure mode the cloud pair (caller rows)
-    const long long key = mode == kStExposure ? (long long)i * n_t + j
+    // bin-pair key, or in exposure and swarm mode the cloud pair (caller rows)
+    const long long key = mode >= kStExposure ? (long long)i * n_t + j
                                               : (long long)q.bin * n_t_bins + t.bin;
     if (filter != nullptr && !set_has(filter, fmask, key)) return -1ll;
     const double cphi = (q.u[0] * t.u[0] + q.u[1] * t.u[1]) + q.u[2] * t.u[2];
     const double s = ((q.E * t.E) * (1.0 - cphi)) / (2.0 * kMe * kMe);
     if (!(s > 1.0)) return -1ll;
+    if (mode == kStMeet) {  // swarms: the swept clouds meet, above threshold
+        sum = 1.0;
+        cnt = 1;
+        return key;
+    }
     const double t_end = ((double)k1 + 1.0) * dt;
     double lo = (double)k0, hi = (double)k1;
 #pragma unroll
@@ -505,7 +510,10 @@ __global__ void __launch_bounds__(64, 4) k_st_traverse(
 // lane's stack. Most of these descents end after a few nodes without a leaf, so there is little
 // that neighbours could share, and a wave per kStQueries queries (k_st_traverse) pays its
 // latency for eight lanes' work: 3e4 macro-particles per beam over 400 steps 7.7 ms that way,
-// 0.8 ms so.
+// 0.8 ms so. While all those waves are on the chip at once (kMeetWaves), that latency is the
+// whole time, and a lane that adds its leaves' pairs one after another is the slower: 24
+// macro-particles that all meet over 10 steps 22 us by waves, 80 by lanes.
+constexpr int64_t kMeetWaves = 4096;  // 256 CUs of 16
 __global__ void __launch_bounds__(256) k_st_meet(
     const Node *__restrict__ nodes, int32_t n_int, const PBox *__restrict__ root_box,
     const PBox *__restrict__ qbox, const uint32_t *__restrict__ qorder, int64_t nq, int64_t m,
@@ -1333,9 +1341,16 @@ void launch_st_traverse(const Node *nodes, int64_t n_int64, const PBox *root_box
 
 void launch_st_meet(const Node *nodes, int64_t n_int, const PBox *root_box, const PBox *qbox,
                     const uint32_t *qorder, int64_t nq, int32_t m, const int32_t *inst_root,
-                    int64_t n_t, const StRec *qrec, const StRec *trec, long long *keys, double *vals,
-                    int64_t cap, DevCounters *c, hipStream_t st) {
+                    int64_t n_t, const StRec *qrec, const StRec *trec, double dt, int32_t k_begin,
+                    int32_t k_last, const StCell &cell, long long *keys, double *vals, int64_t cap,
+                    double *slots, DevCounters *c, hipStream_t st) {
     if (nq <= 0 || m <= 0 || n_int < 0) return;
+    if ((nq + kStQueries - 1) / kStQueries * m <= kMeetWaves) {
+        launch_st_traverse(nodes, n_int, root_box, qbox, qorder, nq, m, inst_root, n_t, qrec, trec, 1,
+                           dt, 1, k_begin, k_last, cell, kStMeet, nullptr, 0, keys, vals, cap, slots,
+                           c, st);
+        return;
+    }
     hipLaunchKernelGGL(k_st_meet, dim3(grid_for(nq * m, 256)), dim3(256), 0, st, nodes,
                        (int32_t)n_int, root_box, qbox, qorder, nq, (int64_t)m, inst_root, n_t, qrec,
                        trec, keys, vals, (uint64_t)(cap - 1), c);

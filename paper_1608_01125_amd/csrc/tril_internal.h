@@ -672,7 +672,7 @@ void launch_st_pack(const BeamDev &b, const int32_t *bins, StRec *rec, hipStream
 // Cloud traversal of m windows of win steps each (window s of the launch covers the steps of
 // [k_begin, k_last] in [(c->step + s) win, (c->step + s + 1) win)) by nq query rows in the
 // order qorder; boxes and hierarchy built with the window as the step. mode: 0 yields,
-// 1 overlap integrals, 2 exposures per cloud pair.
+// 1 overlap integrals, 2 exposures per cloud pair, 3 swept clouds that meet (win 1).
 void launch_st_traverse(const Node *nodes, int64_t n_int, const PBox *root_box, const PBox *qbox,
                         const uint32_t *qorder, int64_t nq, int32_t m, const int32_t *inst_root,
                         int64_t n_t, const StRec *qrec, const StRec *trec, int64_t n_t_bins,
@@ -684,8 +684,9 @@ void launch_st_traverse(const Node *nodes, int64_t n_int, const PBox *root_box, 
 // step), each a key i n_t + j of the table.
 void launch_st_meet(const Node *nodes, int64_t n_int, const PBox *root_box, const PBox *qbox,
                     const uint32_t *qorder, int64_t nq, int32_t m, const int32_t *inst_root,
-                    int64_t n_t, const StRec *qrec, const StRec *trec, long long *keys, double *vals,
-                    int64_t cap, DevCounters *c, hipStream_t st);
+                    int64_t n_t, const StRec *qrec, const StRec *trec, double dt, int32_t k_begin,
+                    int32_t k_last, const StCell &cell, long long *keys, double *vals, int64_t cap,
+                    double *slots, DevCounters *c, hipStream_t st);
 
 // ------------------------------------------------------------ annihilation mode
 // Scratch of annihilate_hits: per raw hit (cap) two sort key/value buffer pairs, rank,

@@ -49,7 +49,8 @@ def _meet(A, B, offA, offB, margin):
 
 @pytest.mark.parametrize("step_batch", [0, 1, 5])
 @pytest.mark.parametrize("sizes", [((1,), (1,)), ((63,), (300,)), ((257,), (129,)),
-                                   ((1, 0, 33, 1, 70), (1, 40, 1, 300, 90)), ((40, 5), (0, 1))])
+                                   ((1, 0, 33, 1, 70), (1, 40, 1, 300, 90)), ((40, 5), (0, 1)),
+                                   ((900, 0, 1, 40), (200, 40, 300, 1))])  # one lane a query
 def test_pairs_whose_swept_clouds_meet(torch, sizes, step_batch):  # noqa: F811
     offA, offB = (np.concatenate([[0], np.cumsum(s)]).astype(np.int64) for s in sizes)
     A, B = _beam(int(offA[-1]), 5, 1.0), _beam(int(offB[-1]), 6, -1.0)
