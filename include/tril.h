@@ -516,6 +516,17 @@ int tril_st_features(tril_ctx *ctx, const double *q_sums, const tril_st_grid *q_
                      const tril_st_sur_params *params, float *x, double *y0, int64_t *key,
                      int64_t cap, int64_t *n);
 
+/* The rows of a tril_st_features call that returned TRIL_E_OVERFLOW, for a caller that
+ * allocates them to size (the call may have had cap 0): n is the number it reported, sums and
+ * grids the same; x, y0 and key as there, room for n each. The context holds the candidate
+ * pairs until this call or the next one that forms features (tril_st_features,
+ * tril_st_surrogate, tril_st_audit); TRIL_E_STATE when it holds no pairs of that number and
+ * those grids (also after an overflow whose pairs found no room on the device: the whole call
+ * with a larger cap remains). Synchronous. */
+int tril_st_feature_rows(tril_ctx *ctx, const double *q_sums, const tril_st_grid *q_grid,
+                         const double *t_sums, const tril_st_grid *t_grid, float *x, double *y0,
+                         int64_t *key, int64_t n);
+
 /* Training targets of feature rows: target[i] = log((Y + eps y0[i]) / y0[i]) with Y the
  * yield of key[i] in an exact table (0 if absent); y_exact (device, or NULL) receives Y.
  * Asynchronous on the HIP stream. */

@@ -142,6 +142,8 @@ struct tril_ctx {
     uint32_t *fs_va = nullptr, *fs_vb = nullptr;
     double *fs_om = nullptr;
     int64_t fs_cap = 0;
+    int64_t fs_held = 0;         // rows that wait for tril_st_feature_rows, and their grids' bins
+    int64_t fs_bins[2] = {0, 0};
     StRec *st_qrec = nullptr, *st_trec = nullptr;  // the cloud traversal's photon records
     int64_t st_qrec_cap = 0, st_trec_cap = 0;
     // surrogate path scratch: bin clouds, bin-pair overlap table, features, exact fallback
@@ -1836,6 +1838,37 @@ int sur_features(tril_ctx *c, const double *q_sums, const tril_st_grid *gq, cons
                  const tril_st_grid *gt, int32_t k0, int32_t n_steps, const tril_st_sur_params *p,
                  int64_t *nrow);
 
+// Buffers of n feature rows: sort keys and values, overlap integrals.
+int ensure_rows(tril_ctx *c, int64_t n) {
+    dev_free(c->fs_ka); dev_free(c->fs_kb); dev_free(c->fs_va); dev_free(c->fs_vb);
+    dev_free(c->fs_om);
+    c->fs_cap = 0;
+    CHK(dev_alloc(&c->fs_ka, (size_t)n)); CHK(dev_alloc(&c->fs_kb, (size_t)n));
+    CHK(dev_alloc(&c->fs_va, (size_t)n)); CHK(dev_alloc(&c->fs_vb, (size_t)n));
+    CHK(dev_alloc(&c->fs_om, (size_t)n));
+    c->fs_cap = n;
+    return TRIL_OK;
+}
+
+// The n compacted pairs' feature rows in ascending key order (the rows feed training, whose
+// minibatches index them). Synchronises.
+int form_rows(tril_ctx *c, const double *q_sums, const tril_st_grid *gq, const double *t_sums,
+              const tril_st_grid *gt, float *x, double *y0, int64_t *key, int64_t n) {
+    const uint64_t max_key = (uint64_t)grid_bins(gq) * (uint64_t)grid_bins(gt) - 1;
+    const int key_bits = std::max(1, bits_for(max_key));
+    CHK(ensure_sort_scratch(c, n));
+    const bool alt = radix_sort_u64(c->fs_ka, c->fs_va, c->fs_kb, c->fs_vb, n, key_bits, c->ss,
+                                    &c->d_cnt->err, c->st);
+    double cell[3];
+    grid_cell(gq, cell);
+    launch_st_features(alt ? c->fs_kb : c->fs_ka, alt ? c->fs_vb : c->fs_va, c->fs_om, n,
+                       grid_bins(gt), q_sums, t_sums, (cell[0] * cell[1]) * cell[2], x, y0,
+                       reinterpret_cast<long long *>(key), c->st);
+    HIPCHK(hipGetLastError());
+    HIPCHK(hipStreamSynchronize(c->st));
+    return TRIL_OK;
+}
+
 // Sum of the per-wave slots (synchronises the stream).
 int slot_sum(tril_ctx *c, double *out) {
     CHK(ensure_st_host(c));
@@ -2139,6 +2172,18 @@ int tril_ip_swarm(tril_ctx *c, const tril_beam *t, const int32_t *t_bins, int64_
     return TRIL_OK;
 }
 
+int tril_st_feature_rows(tril_ctx *c, const double *q_sums, const tril_st_grid *gq,
+                         const double *t_sums, const tril_st_grid *gt, float *x, double *y0,
+                         int64_t *key, int64_t n) {
+    if (!c || !q_sums || !t_sums || n < 1 || !x || !y0 || !key) return TRIL_E_INVAL;
+    CHK(check_grid(gq));
+    CHK(check_grid(gt));
+    if (n != c->fs_held || grid_bins(gq) != c->fs_bins[0] || grid_bins(gt) != c->fs_bins[1])
+        return TRIL_E_STATE;
+    c->fs_held = 0;
+    return form_rows(c, q_sums, gq, t_sums, gt, x, y0, key, n);
+}
+
 int tril_st_features(tril_ctx *c, const double *q_sums, const tril_st_grid *gq,
                      const double *t_sums, const tril_st_grid *gt, int32_t k0, int32_t n_steps,
                      const tril_st_sur_params *p, float *x, double *y0, int64_t *key, int64_t cap,
@@ -2146,6 +2191,7 @@ int tril_st_features(tril_ctx *c, const double *q_sums, const tril_st_grid *gq,
     if (!c || !q_sums || !t_sums || !n || cap < 0 || (cap > 0 && (!x || !y0 || !key)) || k0 < 0 ||
         n_steps < 0)
         return TRIL_E_INVAL;
+    c->fs_held = 0;
     CHK(check_grid(gq));
     CHK(check_grid(gt));
     const double factor = (p && p->cloud_factor > 0.0) ? p->cloud_factor : 3.5;
@@ -2184,8 +2230,7 @@ int tril_st_features(tril_ctx *c, const double *q_sums, const tril_st_grid *gq,
         if (attempt >= 3) return TRIL_E_NOMEM;  // the pair table did not fit the scratch it may take
         tcap = c->sg_cap * 4;
     }
-    // one feature row per occupied slot, in ascending key order (the rows feed training, whose
-    // minibatches index them); the sort's buffers stay with the context
+    // one feature row per occupied slot; the rows' buffers stay with the context
     CHK(ensure_st_count(c));
     int64_t nr = 0;
     for (int attempt = 0;; ++attempt) {
@@ -2195,31 +2240,19 @@ int tril_st_features(tril_ctx *c, const double *q_sums, const tril_st_grid *gq,
         HIPCHK(hipGetLastError());
         CHK(read_st_count(c, &nr));
         *n = nr;
-        if (nr > cap) return TRIL_E_OVERFLOW;
-        if (nr >= ((int64_t)1 << 32)) return TRIL_E_INVAL;
+        if (nr >= ((int64_t)1 << 32)) return nr > cap ? TRIL_E_OVERFLOW : TRIL_E_INVAL;
         if (nr <= c->fs_cap) break;
         if (attempt > 0) return TRIL_E_INTERNAL;
-        dev_free(c->fs_ka); dev_free(c->fs_kb); dev_free(c->fs_va); dev_free(c->fs_vb);
-        dev_free(c->fs_om);
-        c->fs_cap = 0;
-        CHK(dev_alloc(&c->fs_ka, (size_t)nr)); CHK(dev_alloc(&c->fs_kb, (size_t)nr));
-        CHK(dev_alloc(&c->fs_va, (size_t)nr)); CHK(dev_alloc(&c->fs_vb, (size_t)nr));
-        CHK(dev_alloc(&c->fs_om, (size_t)nr));
-        c->fs_cap = nr;
+        const int r = ensure_rows(c, nr);
+        if (r != TRIL_OK) return nr > cap ? TRIL_E_OVERFLOW : r;
     }
-    if (nr == 0) return TRIL_OK;
-    const uint64_t max_key = (uint64_t)grid_bins(gq) * (uint64_t)grid_bins(gt) - 1;
-    const int key_bits = std::max(1, bits_for(max_key));
-    CHK(ensure_sort_scratch(c, nr));
-    const bool alt = radix_sort_u64(c->fs_ka, c->fs_va, c->fs_kb, c->fs_vb, nr, key_bits, c->ss,
-                                    &c->d_cnt->err, c->st);
-    const double vol = (cq[0] * cq[1]) * cq[2];
-    launch_st_features(alt ? c->fs_kb : c->fs_ka, alt ? c->fs_vb : c->fs_va, c->fs_om, nr,
-                       grid_bins(gt), q_sums, t_sums, vol, x, y0, reinterpret_cast<long long *>(key),
-                       c->st);
-    HIPCHK(hipGetLastError());
-    HIPCHK(hipStreamSynchronize(c->st));
-    return TRIL_OK;
+    if (nr > cap) {  // the rows wait for tril_st_feature_rows
+        c->fs_held = nr;
+        c->fs_bins[0] = grid_bins(gq);
+        c->fs_bins[1] = grid_bins(gt);
+        return TRIL_E_OVERFLOW;
+    }
+    return nr > 0 ? form_rows(c, q_sums, gq, t_sums, gt, x, y0, key, nr) : TRIL_OK;
 }
 
 int tril_st_targets(const int64_t *key, const double *y0, int64_t n, const tril_st_table *exact,

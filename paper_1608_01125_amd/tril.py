@@ -135,8 +135,8 @@ EXPORTS = ("tril_create", "tril_build", "tril_collide", "tril_run", "tril_stats"
            "tril_st_exact_depleted", "tril_ip_swarm",
            "tril_mlp_create", "tril_mlp_destroy", "tril_mlp_set_params", "tril_mlp_get_params",
            "tril_mlp_set_norm", "tril_mlp_fit_norm", "tril_mlp_grad", "tril_mlp_train",
-           "tril_mlp_predict", "tril_st_features", "tril_st_targets", "tril_st_surrogate",
-           "tril_st_audit", "tril_st_calibrate", "tril_dbg_st_audit_sample",
+           "tril_mlp_predict", "tril_st_features", "tril_st_feature_rows", "tril_st_targets",
+           "tril_st_surrogate", "tril_st_audit", "tril_st_calibrate", "tril_dbg_st_audit_sample",
            "tril_dbg_gemm_bf16",
            "tril_reset_counters", "tril_destroy", "tril_strerror", "tril_last_hip_error",
            "tril_dbg_sort_u32", "tril_dbg_sort_u64", "tril_dbg_morton", "tril_dbg_pair_eval",
@@ -200,6 +200,7 @@ def lib() -> ctypes.CDLL:
     gp = ctypes.POINTER(tril_st_grid)
     L.tril_st_features.argtypes = [vp, vp, gp, vp, gp, i32, i32, ctypes.POINTER(tril_st_sur_params),
                                    vp, vp, vp, i64, ctypes.POINTER(ctypes.c_int64)]
+    L.tril_st_feature_rows.argtypes = [vp, vp, gp, vp, gp, vp, vp, vp, i64]
     L.tril_st_targets.argtypes = [vp, vp, i64, ctypes.POINTER(tril_st_table), ctypes.c_double, vp,
                                   vp, vp]
     L.tril_st_surrogate.argtypes = [vp, vp, ctypes.POINTER(tril_beam), vp, vp, gp,
@@ -649,27 +650,33 @@ def tril_dbg_st_audit_sample(ctx, side: int, cap: int):
 def tril_st_features(ctx, q_sums, q_grid, t_sums, t_grid, k0: int, n_steps: int, params=None,
                      cap: int = 1 << 20):
     """Feature rows of the candidate bin pairs: (x [n, 6] float32, y0 [n] float64,
-    key [n] int64), device tensors; grows the buffers once if cap is too small (the first
-    attempt has room for 2^23 rows at least: a second one repeats the pass over the cells)."""
+    key [n] int64), device tensors of exactly the rows: they are counted first and formed into
+    tensors of that size. cap is not needed for that (negative: refused, as in the library)."""
     import torch
     gq, gt = st_grid(q_grid), st_grid(t_grid)
     p = params or sur_params()
-    cap = max(int(cap), 1 << 23)
-    for _ in range(2):
-        x = torch.empty((max(cap, 1), 6), dtype=torch.float32, device="cuda")
-        y0 = torch.empty(max(cap, 1), dtype=torch.float64, device="cuda")
-        key = torch.empty(max(cap, 1), dtype=torch.int64, device="cuda")
-        n = ctypes.c_int64(0)
-        code = lib().tril_st_features(_h(ctx), q_sums.data_ptr(), ctypes.byref(gq), t_sums.data_ptr(),
-                                      ctypes.byref(gt), int(k0), int(n_steps), ctypes.byref(p),
-                                      x.data_ptr(), y0.data_ptr(), key.data_ptr(), cap, ctypes.byref(n))
-        if code == TRIL_E_OVERFLOW and n.value > cap:
-            cap = n.value
-            continue
-        _check(code, f"tril_st_features (rows {n.value}, capacity {cap})")
-        m = n.value
-        return x[:m], y0[:m], key[:m]
-    raise TrilError(TRIL_E_OVERFLOW, "tril_st_features")
+    n = ctypes.c_int64(0)
+
+    def call(x, y0, key, room):
+        return lib().tril_st_features(_h(ctx), q_sums.data_ptr(), ctypes.byref(gq), t_sums.data_ptr(),
+                                      ctypes.byref(gt), int(k0), int(n_steps), ctypes.byref(p), x, y0,
+                                      key, room, ctypes.byref(n))
+
+    code = call(None, None, None, min(int(cap), 0))
+    if code != TRIL_E_OVERFLOW:
+        _check(code, "tril_st_features")  # TRIL_OK: no rows
+    m = n.value
+    x = torch.empty((m, 6), dtype=torch.float32, device="cuda")
+    y0 = torch.empty(m, dtype=torch.float64, device="cuda")
+    key = torch.empty(m, dtype=torch.int64, device="cuda")
+    if m > 0:
+        out = x.data_ptr(), y0.data_ptr(), key.data_ptr()
+        code = lib().tril_st_feature_rows(_h(ctx), q_sums.data_ptr(), ctypes.byref(gq),
+                                          t_sums.data_ptr(), ctypes.byref(gt), *out, m)
+        if code == TRIL_E_STATE:  # the counted pairs found no room beside the table
+            code = call(*out, m)
+        _check(code, f"tril_st_features (rows {n.value}, capacity {m})")
+    return x, y0, key
 
 
 def tril_st_targets(key, y0, exact: "StTable", eps: float = 1e-3, stream=None):
