@@ -80,12 +80,8 @@ constexpr int64_t kBatchStepsMin = 32;
 // pairs that never overlap and leave fewer waves. Training rows of 2e4 clouds per beam and the
 // audit of 2e5, 16 queries per wave: 17.4 and 43.8 ms at 4 steps, 13.0 and 32.4 at 8, 11.0 and
 // 26.8 at 16, 11.3 and 27.9 at 32, 12.6 and 29.3 at 64; with 8 queries per wave, as now, 8.93 and
-// 22.1 at 16, 8.69 and 21.7 at 32. These are steps of a fifth of the cloud's shortest edge. The
-// boxes of clouds that cross at an angle grow with the square of the window's length, the pairs
-// that overlap only with the length, so a window is no longer than kStWinEdges such edges: 1e5
-// clouds per beam at 90 degrees take 55.3 ms per pass with steps of 4 edges in windows of 32, 6.8
-// step by step; steps of one edge 43.1 ms in windows of 32, 20.8 of 8 and 16.5 of 4 (head-on
-// beams 12.4, 13.0 and 15.0 ms).
+// 22.1 at 16, 8.69 and 21.7 at 32. (Steps of a fifth of the cloud's shortest edge; windows longer
+// than kStWinEdges such edges are not taken unseen, see st_window.)
 constexpr int64_t kStWin = 32;
 constexpr double kStWinEdges = 6.5;
 // with window copies (the plain regime) a launch's tree buffers hold a copy per window, not
@@ -1641,6 +1637,61 @@ int ensure_st_rec(tril_ctx *c, StRec *&rec, int64_t &cap, int64_t n) {
     return TRIL_OK;
 }
 
+// Steps per window of clouds that move several edges in `longest` steps: longest, its half, its
+// quarter, .. or 1. A window costs each query a descent, worth kStDescent pairs, and the pairs
+// whose boxes, swept over the window, meet; those grow with the window as the sum of the two
+// boxes' extents on every axis does, linearly for head-on beams and up to quadratically for
+// crossing ones. The targets' density is taken as even over their bounding box, ten times too low
+// for the core of a Gaussian beam; kStDescent makes up for half of that. Over 216 settings
+// (Gaussian and even beams of 3e3 to 1e5 clouds at 40 to 180 degrees, steps of a fifth of an edge
+// to 50 edges) this choice took 1.09 times as long as the best window on average and 1.7 times at
+// worst, windows of 32 always 1.75 and 32 times. 1e5 clouds per beam at 90 degrees, steps of 4
+// edges: 6.1 ms in windows of 1 or 2 steps, 55 in windows of 32; 3e4 clouds of 0.02 um, steps of 5
+// edges: 7.7 ms in windows of 1, 1.5 of 32. Reads the two beams' statistics back (synchronises).
+constexpr double kStDescent = 15.0;
+
+int st_window(tril_ctx *c, const tril_beam *t, const tril_beam *q, const double cell[3],
+              int32_t longest, int32_t *win) {
+    const size_t k = (size_t)t->n_inst;
+    std::vector<InstStats> st(2 * k);
+    HIPCHK(hipMemcpyAsync(st.data(), c->t_stats, k * sizeof(InstStats), hipMemcpyDeviceToHost, c->st));
+    HIPCHK(hipMemcpyAsync(st.data() + k, c->q_stats, k * sizeof(InstStats), hipMemcpyDeviceToHost,
+                          c->st));
+    HIPCHK(hipStreamSynchronize(c->st));
+    auto val = [](unsigned long long u) {  // of an order-preserving key (d2ord)
+        const unsigned long long b = (u >> 63) ? (u & ~(1ull << 63)) : ~u;
+        double d;
+        std::memcpy(&d, &b, sizeof(d));
+        return d;
+    };
+    auto rows = [](const tril_beam *b, size_t i) {
+        return (double)(b->n_inst > 1 ? b->inst_off[i + 1] - b->inst_off[i] : b->n);
+    };
+    double best = 0.0;
+    for (int32_t w = longest;; w /= 2) {
+        const double len = (double)(w - 1) * c->dt;  // from the first mid-step to the last
+        double cost = 0.0;
+        for (size_t i = 0; i < k; ++i) {
+            const InstStats &a = st[i], &b = st[k + i];
+            if (a.mn[0] > a.mx[0] || b.mn[0] > b.mx[0]) continue;  // no usable photon
+            double vol = 1.0, room = 1.0;
+            for (int x = 0; x < 3; ++x) {
+                const double u = std::max(std::fabs(val(a.mn[3 + x])), std::fabs(val(a.mx[3 + x]))) +
+                                 std::max(std::fabs(val(b.mn[3 + x])), std::fabs(val(b.mx[3 + x])));
+                vol *= 2.0 * cell[x] + u * len;
+                room *= cell[x] + (val(a.mx[x]) - val(a.mn[x]));
+            }
+            const double nt = rows(t, i);
+            cost += rows(q, i) * (kStDescent + std::min(nt, nt * (vol / room))) / (double)w;
+        }
+        if (w == longest || cost < best) {
+            best = cost;
+            *win = w;
+        }
+        if (w == 1) return TRIL_OK;
+    }
+}
+
 // Statistical-regime pass over steps k0 .. k0+n_steps-1 (asynchronous): clouds of edges
 // `cell` in a hierarchy per window of steps, yields (or by `mode` overlap integrals,
 // exposures, meetings) added to the table under (q_bins[i], t_bins[j]) or the cloud pair;
@@ -1655,10 +1706,21 @@ int st_run(tril_ctx *c, const tril_beam *t, const int32_t *t_bins, int64_t n_t_b
     const int32_t ms = n_steps > 0 ? pick_batch(c, t, q, n_steps) : 1;
     // swarms (mode 3) keep a descent per step: their pairs are those whose clouds, swept over
     // one step, meet
+    int32_t win = mode == 3 ? 1 : (int32_t)std::min<int64_t>(kStWin, std::max(1, std::min(n_steps, ms)));
     const double edge = std::min(cell[0], std::min(cell[1], cell[2]));
-    const int64_t longest = (int64_t)std::min((double)kStWin, kStWinEdges * edge / c->dt);
-    const int32_t win =
-        mode == 3 ? 1 : (int32_t)std::max<int64_t>(1, std::min<int64_t>(longest, std::min(n_steps, ms)));
+    const bool look = (double)win * c->dt > kStWinEdges * edge && win > 1;
+    // caller photons must be light-like; the bin clouds of the surrogate's geometric pass
+    // (mode 1) carry mean directions
+    const bool light_like = mode != 1;
+    if (look) {
+        CHK(ensure_target(c, t->n, t->n, t->n_inst, t->n_inst));
+        CHK(ensure_query(c, q->n, q->n, q->n_inst, q->n_inst));
+        CHK(upload_offsets(c, t, c->d_t_off, c->h_t_off));
+        CHK(upload_offsets(c, q, c->d_q_off, c->h_q_off));
+        launch_beam_stats(view(t, c->d_t_off, 1), c->t_spart, c->t_stats, c->d_cnt, c->st, light_like);
+        launch_beam_stats(view(q, c->d_q_off, 1), c->q_spart, c->q_stats, c->d_cnt, c->st, light_like);
+        CHK(st_window(c, t, q, cell, win, &win));
+    }
     // windows are aligned to multiples of their length; the first and the last may be cut
     const int64_t kw0 = k0 / win;
     const int64_t n_win = n_steps > 0 ? (k0 + (int64_t)n_steps - 1) / win - kw0 + 1 : 0;
@@ -1672,10 +1734,10 @@ int st_run(tril_ctx *c, const tril_beam *t, const int32_t *t_bins, int64_t n_t_b
     c->nt = t->n;
     c->q_order_key = nullptr;
     const BeamDev t1 = view(t, c->d_t_off, 1), q1 = view(q, c->d_q_off, 1);
-    // caller photons must be light-like; the bin clouds of the surrogate's geometric pass
-    // (mode 1) carry mean directions
-    launch_beam_stats(t1, c->t_spart, c->t_stats, c->d_cnt, c->st, mode != 1);
-    launch_beam_stats(q1, c->q_spart, c->q_stats, c->d_cnt, c->st, mode != 1);
+    if (!look) {
+        launch_beam_stats(t1, c->t_spart, c->t_stats, c->d_cnt, c->st, light_like);
+        launch_beam_stats(q1, c->q_spart, c->q_stats, c->d_cnt, c->st, light_like);
+    }
     launch_st_pack(t1, t_bins, c->st_trec, c->st);
     launch_st_pack(q1, q_bins, c->st_qrec, c->st);
     const StCell sc{{cell[0], cell[1], cell[2]}};
