@@ -1647,11 +1647,13 @@ int ensure_st_rec(tril_ctx *c, StRec *&rec, int64_t &cap, int64_t n) {
 // to 50 edges) this choice took 1.09 times as long as the best window on average and 1.7 times at
 // worst, windows of 32 always 1.75 and 32 times. 1e5 clouds per beam at 90 degrees, steps of 4
 // edges: 6.1 ms in windows of 1 or 2 steps, 55 in windows of 32; 3e4 clouds of 0.02 um, steps of 5
-// edges: 7.7 ms in windows of 1, 1.5 of 32. Reads the two beams' statistics back (synchronises).
-constexpr double kStDescent = 15.0;
+// edges: 7.7 ms in windows of 1, 1.5 of 32. In windows of one step a lane per query (*lanes)
+// descends for a fifth of a wave's cost and takes several times as long per pair. Reads the two
+// beams' statistics back (synchronises).
+constexpr double kStDescent = 15.0, kStLaneDescent = 3.0, kStLanePair = 40.0;
 
 int st_window(tril_ctx *c, const tril_beam *t, const tril_beam *q, const double cell[3],
-              int32_t longest, int32_t *win) {
+              int32_t longest, int32_t *win, bool *lanes) {
     const size_t k = (size_t)t->n_inst;
     std::vector<InstStats> st(2 * k);
     HIPCHK(hipMemcpyAsync(st.data(), c->t_stats, k * sizeof(InstStats), hipMemcpyDeviceToHost, c->st));
@@ -1670,7 +1672,7 @@ int st_window(tril_ctx *c, const tril_beam *t, const tril_beam *q, const double 
     double best = 0.0;
     for (int32_t w = longest;; w /= 2) {
         const double len = (double)(w - 1) * c->dt;  // from the first mid-step to the last
-        double cost = 0.0;
+        double cost = 0.0, by_lanes = 0.0;
         for (size_t i = 0; i < k; ++i) {
             const InstStats &a = st[i], &b = st[k + i];
             if (a.mn[0] > a.mx[0] || b.mn[0] > b.mx[0]) continue;  // no usable photon
@@ -1681,14 +1683,18 @@ int st_window(tril_ctx *c, const tril_beam *t, const tril_beam *q, const double 
                 vol *= 2.0 * cell[x] + u * len;
                 room *= cell[x] + (val(a.mx[x]) - val(a.mn[x]));
             }
-            const double nt = rows(t, i);
-            cost += rows(q, i) * (kStDescent + std::min(nt, nt * (vol / room))) / (double)w;
+            const double nt = rows(t, i), met = std::min(nt, nt * (vol / room));
+            cost += rows(q, i) * (kStDescent + met) / (double)w;
+            by_lanes += rows(q, i) * (kStLaneDescent + kStLanePair * met);
         }
         if (w == longest || cost < best) {
             best = cost;
             *win = w;
         }
-        if (w == 1) return TRIL_OK;
+        if (w > 1) continue;
+        *lanes = by_lanes < best;
+        if (*lanes) *win = 1;
+        return TRIL_OK;
     }
 }
 
@@ -1709,6 +1715,7 @@ int st_run(tril_ctx *c, const tril_beam *t, const int32_t *t_bins, int64_t n_t_b
     int32_t win = mode == 3 ? 1 : (int32_t)std::min<int64_t>(kStWin, std::max(1, std::min(n_steps, ms)));
     const double edge = std::min(cell[0], std::min(cell[1], cell[2]));
     const bool look = (double)win * c->dt > kStWinEdges * edge && win > 1;
+    bool lanes = mode == 3;
     // caller photons must be light-like; the bin clouds of the surrogate's geometric pass
     // (mode 1) carry mean directions
     const bool light_like = mode != 1;
@@ -1719,7 +1726,7 @@ int st_run(tril_ctx *c, const tril_beam *t, const int32_t *t_bins, int64_t n_t_b
         CHK(upload_offsets(c, q, c->d_q_off, c->h_q_off));
         launch_beam_stats(view(t, c->d_t_off, 1), c->t_spart, c->t_stats, c->d_cnt, c->st, light_like);
         launch_beam_stats(view(q, c->d_q_off, 1), c->q_spart, c->q_stats, c->d_cnt, c->st, light_like);
-        CHK(st_window(c, t, q, cell, win, &win));
+        CHK(st_window(c, t, q, cell, win, &win, &lanes));
     }
     // windows are aligned to multiples of their length; the first and the last may be cut
     const int64_t kw0 = k0 / win;
@@ -1758,10 +1765,11 @@ int st_run(tril_ctx *c, const tril_beam *t, const int32_t *t_bins, int64_t n_t_b
         if ((rc = enqueue_build(c, c->st, false)) != TRIL_OK) break;
         launch_prologue(c->d_cnt, 1, c->box_steps, c->st);
         if ((rc = enqueue_query_prep(c, qv, c->st, true)) != TRIL_OK) break;
-        if (mode == 3)
-            launch_st_meet(c->nodes, c->n_int, c->root_box, c->q_box, c->q_order, q->n, mb,
-                           c->inst_root, t->n, c->st_qrec, c->st_trec, c->dt, k0,
-                           k0 + n_steps - 1, sc, keys, vals, cap, c->st_slots, c->d_cnt, c->st);
+        if (lanes)
+            launch_st_lanes(c->nodes, c->n_int, c->root_box, c->q_box, c->q_order, q->n, mb,
+                            c->inst_root, t->n, c->st_qrec, c->st_trec, n_t_bins, c->dt, k0,
+                            k0 + n_steps - 1, sc, mode, filter, filter_cap, keys, vals, cap,
+                            c->st_slots, c->d_cnt, c->st);
         else
             launch_st_traverse(c->nodes, c->n_int, c->root_box, c->q_box, c->q_order, q->n, mb,
                                c->inst_root, t->n, c->st_qrec, c->st_trec, n_t_bins, c->dt, win, k0,

@@ -550,21 +550,26 @@ __global__ void __launch_bounds__(64, 4) k_st_traverse(
     }
 }
 
-// Swarms: cloud pairs above threshold whose boxes, swept over one step, meet, each a key of the
-// table (its value counts the steps). One lane per query and step descends by itself, one load
-// per overlapped internal node, both children tested from it, pending right children on the
-// lane's stack. Most of these descents end after a few nodes without a leaf, so there is little
-// that neighbours could share, and a wave per kStQueries queries (k_st_traverse) pays its
-// latency for eight lanes' work: 3e4 macro-particles per beam over 400 steps 7.7 ms that way,
-// 0.8 ms so. While all those waves are on the chip at once (kMeetWaves), that latency is the
-// whole time, and a lane that adds its leaves' pairs one after another is the slower: 24
-// macro-particles that all meet over 10 steps 22 us by waves, 80 by lanes.
+// The cloud traversal of windows of one step by a lane per query and step, which descends by
+// itself, one load per overlapped internal node, both children tested from it, pending right
+// children on the lane's stack, and evaluates its leaves' pairs one after another. It is the
+// better one where most descents end after a few nodes without a leaf: there is little that
+// neighbours could share, and a wave per kStQueries queries (k_st_traverse) pays its latency for
+// eight lanes' work. Swarms (their table's values count the steps in which two clouds meet): 3e4
+// macro-particles per beam over 400 steps 7.7 ms by waves, 0.8 ms so. Yields: 1e5 clouds of 0.02
+// um per beam at 90 degrees, steps of 50 edges, 3.4 ms by waves (1.8 in windows of 4 steps), 0.9
+// ms so. Where all those waves are on the chip at once (kMeetWaves), their latency is the whole
+// time, and a lane that adds up its pairs one after another the slower: 24 macro-particles that
+// all meet over 10 steps 22 us by waves, 80 by lanes.
 constexpr int64_t kMeetWaves = 4096;  // 256 CUs of 16
-__global__ void __launch_bounds__(256) k_st_meet(
+template <bool kMeets>
+__global__ void __launch_bounds__(256) k_st_lanes(
     const Node *__restrict__ nodes, int32_t n_int, const PBox *__restrict__ root_box,
     const PBox *__restrict__ qbox, const uint32_t *__restrict__ qorder, int64_t nq, int64_t m,
     const int32_t *__restrict__ inst_root, int64_t n_t, const StRec *__restrict__ qrec,
-    const StRec *__restrict__ trec, long long *keys, double *vals, uint64_t mask, DevCounters *c) {
+    const StRec *__restrict__ trec, int64_t n_t_bins, double dt, StCell cell, int mode,
+    const long long *__restrict__ filter, uint64_t fmask, long long *keys, double *vals,
+    uint64_t mask, double *__restrict__ slots, DevCounters *c) {
     const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     const int64_t so = e / nq;  // step of the launch
     int64_t i = 0;
@@ -579,16 +584,20 @@ __global__ void __launch_bounds__(256) k_st_meet(
         tag = __float_as_int(a.w);
         if (tag >= 0 && qrec[i].bin >= 0) node = inst_root[tag];
     }
+    const int32_t k = (int32_t)(c->step + so);
+    const double V = (cell.c[0] * cell.c[1]) * cell.c[2];
+    const double inv_dt = 1.0 / dt, inv_vv = 1.0 / (V * V);
+    double total = 0.0;
     uint32_t visits = 0, n_pairs = 0;
     auto leaf = [&](int32_t link) {
-        const int64_t j = link_elem(link) - so * n_t;
-        const StRec &q = qrec[i], &t = trec[j];
-        if (t.bin < 0) return;
-        const double cphi = (q.u[0] * t.u[0] + q.u[1] * t.u[1]) + q.u[2] * t.u[2];
-        const double s = ((q.E * t.E) * (1.0 - cphi)) / (2.0 * kMe * kMe);
-        if (!(s > 1.0)) return;
-        ++n_pairs;
-        table_add(keys, vals, mask, i * n_t + j, 1.0, &c->err);
+        double sum;
+        uint32_t n;
+        const long long key =
+            st_pair(qrec[i], i, k, k, trec, link_elem(link) - so * n_t, n_t, dt, inv_dt, inv_vv, cell,
+                    kMeets ? (int)kStMeet : mode, n_t_bins, kMeets ? nullptr : filter, fmask, sum, n);
+        n_pairs += n;
+        total += sum;
+        if (key >= 0) table_add(keys, vals, mask, key, sum, &c->err);
     };
     if (node <= -2) {  // an instance of one row: its root is that leaf
         const float4 *lp = reinterpret_cast<const float4 *>(root_box + tag);
@@ -609,8 +618,11 @@ __global__ void __launch_bounds__(256) k_st_meet(
         ++visits;
         const int32_t lc = __float_as_int(l0.w), rc = __float_as_int(r0.w);
         const bool ovl = st_overlap(qb, l0, l1), ovr = st_overlap(qb, r0, r1);
-        if (ovl && lc < 0) leaf(lc);
-        if (ovr && rc < 0) leaf(rc);
+#pragma unroll 1
+        for (int side = 0; side < 2; ++side) {
+            const int32_t ch = side ? rc : lc;
+            if ((side ? ovr : ovl) && ch < 0) leaf(ch);
+        }
         const bool gol = ovl && lc >= 0, gor = ovr && rc >= 0;
         if (gol) {
             if (gor) {
@@ -633,11 +645,13 @@ __global__ void __launch_bounds__(256) k_st_meet(
     for (int off = 32; off >= 1; off >>= 1) {
         v += __shfl_xor(v, off);
         np_ += __shfl_xor(np_, off);
+        total += __shfl_xor(total, off);
     }
     if ((threadIdx.x & 63) == 0) {
         const int slot = blockIdx.x & (kCounterSlots - 1);
         if (v) atomicAdd(&c->visits[slot], v);
         if (np_) atomicAdd(&c->st_pairs[slot], np_);
+        if (total != 0.0) atomicAdd(&slots[slot], total);
     }
 }
 
@@ -1394,21 +1408,29 @@ void launch_st_traverse(const Node *nodes, int64_t n_int64, const PBox *root_box
                            keys, vals, (uint64_t)(cap - 1), slots, c);
 }
 
-void launch_st_meet(const Node *nodes, int64_t n_int, const PBox *root_box, const PBox *qbox,
-                    const uint32_t *qorder, int64_t nq, int32_t m, const int32_t *inst_root,
-                    int64_t n_t, const StRec *qrec, const StRec *trec, double dt, int32_t k_begin,
-                    int32_t k_last, const StCell &cell, long long *keys, double *vals, int64_t cap,
-                    double *slots, DevCounters *c, hipStream_t st) {
+void launch_st_lanes(const Node *nodes, int64_t n_int, const PBox *root_box, const PBox *qbox,
+                     const uint32_t *qorder, int64_t nq, int32_t m, const int32_t *inst_root,
+                     int64_t n_t, const StRec *qrec, const StRec *trec, int64_t n_t_bins, double dt,
+                     int32_t k_begin, int32_t k_last, const StCell &cell, int mode,
+                     const long long *filter, int64_t filter_cap, long long *keys, double *vals,
+                     int64_t cap, double *slots, DevCounters *c, hipStream_t st) {
     if (nq <= 0 || m <= 0 || n_int < 0) return;
     if ((nq + kStQueries - 1) / kStQueries * m <= kMeetWaves) {
-        launch_st_traverse(nodes, n_int, root_box, qbox, qorder, nq, m, inst_root, n_t, qrec, trec, 1,
-                           dt, 1, k_begin, k_last, cell, kStMeet, nullptr, 0, keys, vals, cap, slots,
-                           c, st);
+        launch_st_traverse(nodes, n_int, root_box, qbox, qorder, nq, m, inst_root, n_t, qrec, trec,
+                           n_t_bins, dt, 1, k_begin, k_last, cell, mode, filter, filter_cap, keys,
+                           vals, cap, slots, c, st);
         return;
     }
-    hipLaunchKernelGGL(k_st_meet, dim3(grid_for(nq * m, 256)), dim3(256), 0, st, nodes,
-                       (int32_t)n_int, root_box, qbox, qorder, nq, (int64_t)m, inst_root, n_t, qrec,
-                       trec, keys, vals, (uint64_t)(cap - 1), c);
+    const dim3 grid(grid_for(nq * m, 256)), block(256);
+    const uint64_t fmask = filter ? (uint64_t)(filter_cap - 1) : 0;
+    if (mode == kStMeet)
+        hipLaunchKernelGGL(k_st_lanes<true>, grid, block, 0, st, nodes, (int32_t)n_int, root_box, qbox,
+                           qorder, nq, (int64_t)m, inst_root, n_t, qrec, trec, n_t_bins, dt, cell,
+                           mode, filter, fmask, keys, vals, (uint64_t)(cap - 1), slots, c);
+    else
+        hipLaunchKernelGGL(k_st_lanes<false>, grid, block, 0, st, nodes, (int32_t)n_int, root_box,
+                           qbox, qorder, nq, (int64_t)m, inst_root, n_t, qrec, trec, n_t_bins, dt,
+                           cell, mode, filter, fmask, keys, vals, (uint64_t)(cap - 1), slots, c);
 }
 
 }  // namespace tril

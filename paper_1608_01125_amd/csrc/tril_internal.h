@@ -680,13 +680,14 @@ void launch_st_traverse(const Node *nodes, int64_t n_int, const PBox *root_box, 
                         const StCell &cell, int mode, const long long *filter,
                         int64_t filter_cap, long long *keys, double *vals, int64_t cap,
                         double *slots, DevCounters *c, hipStream_t st);
-// Cloud pairs above threshold whose boxes meet in any of the m steps of the hierarchy (a box per
-// step), each a key i n_t + j of the table.
-void launch_st_meet(const Node *nodes, int64_t n_int, const PBox *root_box, const PBox *qbox,
-                    const uint32_t *qorder, int64_t nq, int32_t m, const int32_t *inst_root,
-                    int64_t n_t, const StRec *qrec, const StRec *trec, double dt, int32_t k_begin,
-                    int32_t k_last, const StCell &cell, long long *keys, double *vals, int64_t cap,
-                    double *slots, DevCounters *c, hipStream_t st);
+// The same for m windows of one step (win 1), by a lane per query and step or, where those are
+// few, by k_st_traverse.
+void launch_st_lanes(const Node *nodes, int64_t n_int, const PBox *root_box, const PBox *qbox,
+                     const uint32_t *qorder, int64_t nq, int32_t m, const int32_t *inst_root,
+                     int64_t n_t, const StRec *qrec, const StRec *trec, int64_t n_t_bins, double dt,
+                     int32_t k_begin, int32_t k_last, const StCell &cell, int mode,
+                     const long long *filter, int64_t filter_cap, long long *keys, double *vals,
+                     int64_t cap, double *slots, DevCounters *c, hipStream_t st);
 
 // ------------------------------------------------------------ annihilation mode
 // Scratch of annihilate_hits: per raw hit (cap) two sort key/value buffer pairs, rank,

@@ -7,6 +7,7 @@ import numpy as np
 import pytest
 
 from paper_1608_01125_amd import beams
+from paper_1608_01125_amd import tril as T
 
 from test_gpu_st_window import _check, _reference, _table, torch  # noqa: F401
 
@@ -48,3 +49,42 @@ def test_sparse_clouds(torch, core, phi, k0, n_steps, step_batch, inst):  # noqa
     if n_steps > 1 and inst == 1:
         assert len(ref[0]) > 30
     _check(got, ref)
+
+
+@pytest.mark.parametrize("phi", [180.0, 90.0])
+@pytest.mark.parametrize("inst", [1, 5])
+def test_steps_of_many_edges(torch, phi, inst):  # noqa: F811
+    """Sparse clouds that move 40 edges per step take a lane per query and step, in launches of one
+    step (375 waves) the shared descent: yields against the oracle, and depleted yields per cloud
+    pair the same by both."""
+    wl, A, B, (ga, gb) = _beams(400, phi)
+    wl = replace(wl, dt=4.0, n_steps=60)
+    offA = offB = None
+    if inst > 1:  # one without targets, one of a single target
+        offA = np.array([0, 900, 901, 1500, 2200, N])
+        offB = np.array([0, 900, 1500, 1500, 1501, N])
+    one = np.array([0, N])
+    ref = _reference(A, B, ga, gb, wl, 0, 60, one if offA is None else offA,
+                     one if offB is None else offB)
+    assert len(ref[0]) > 30
+    for step_batch in (0, 1):
+        _check(_table(torch, A, B, ga, gb, wl, 0, 60, offA, offB, step_batch=step_batch), ref)
+    sides = []
+    for X, g, off in ((A, ga, offA), (B, gb, offB)):
+        b, bins = T.Beam(X, off), torch.empty(N, dtype=torch.int32, device="cuda")
+        T.tril_st_bin(b, g, bins)
+        sides.append((b, bins))
+    got = []
+    for step_batch in (0, 1):
+        ctx, tab, pt = T.Context(wl.dt, None, step_batch=step_batch), T.StTable(18), T.StTable(18)
+        try:
+            tot = T.tril_st_exact_depleted(ctx, *sides[1], gb.n_bins, *sides[0], ga.cell, 0, 60, pt, tab)
+        finally:
+            ctx.close()
+        got.append((*pt.items(), *tab.items(), tot))
+    assert len(got[0][0]) > 30
+    for a, b in zip(got[0][:4:2], got[1][:4:2]):
+        assert np.array_equal(a, b)
+    for a, b in zip(got[0][1:4:2], got[1][1:4:2]):
+        np.testing.assert_allclose(a, b, rtol=1e-12, atol=0)
+    assert got[0][4] == pytest.approx(got[1][4], rel=1e-12)
