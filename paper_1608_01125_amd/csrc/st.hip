@@ -305,8 +305,9 @@ constexpr int kStStack = 1024;  // pending nodes of a wave
 constexpr int kStDepth = 128;   // deeper than any radix tree over (key, index) pairs
 // A wave's hull of more than this many times its widest query box's volume is loose (its nodes
 // are tested against the boxes too). Training rows of 2e4 clouds per beam and the audit of 2e5:
-// 4.27 and 16.5 ms with the hull alone, 4.17 and 16.7 with the boxes always, 4.13 and 16.6 above
-// 4 volumes, 4.05 and 16.3 above 16, 4.04 and 16.3 above 64, 4.09 and 16.3 above 512.
+// 4.27 and 16.5 ms with the hull alone, 3.95 and 15.9 so (with the boxes' tests in a loop: 4.17 and
+// 16.7 always, 4.13 and 16.6 above 4 volumes, 4.05 and 16.3 above 16, 4.04 and 16.3 above 64, 4.09
+// and 16.3 above 512).
 constexpr float kStLoose = 16.0f;
 // Waves of one launch: a grid holds at most 2^32 - 1 threads, and eight per query and window
 // pass that from 2^29 queries times windows (the windows of one build times the query beam).
@@ -488,7 +489,7 @@ __global__ void __launch_bounds__(64, 4) k_st_traverse(
                 ovr = st_overlap(hull, r0v, r1);
                 if (loose && (ovl || ovr)) {
                     bool al = false, ar = false;
-#pragma unroll 1
+#pragma unroll  // (in a loop, the boxes' reads wait for one another: rows 4.05 ms, audit 16.2)
                     for (int j = 0; j < kStQueries; ++j) {
                         const float4 a = s_box[j][0], b = s_box[j][1];
                         const float q[6] = {a.x, a.y, a.z, b.x, b.y, b.z};
