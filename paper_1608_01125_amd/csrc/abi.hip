@@ -665,7 +665,8 @@ int enqueue_build(tril_ctx *c, hipStream_t st, bool timed, bool presorted = fals
     const bool shear = q_stats != nullptr && c->quad && !c->keep_nodes &&
                        descent_window(c, win) >= kShearSteps;
     if (win > 1)
-        launch_win_bounds(c->t_stats, t.n_inst, c->dt, shear ? q_stats : nullptr, c->t_wb, st);
+        launch_win_bounds(c->t_stats, t, c->dt, shear ? q_stats : nullptr,
+                          (double)descent_window(c, win) * c->dt, c->t_wb, st);
     launch_inst_roots(t, c->cloud, c->box_dt, c->inst_base, rows, c->inst_root, c->root_box, c->d_cnt,
                       st, win, c->t_rec);
     int32_t *xbase = nullptr;

@@ -442,9 +442,10 @@ void launch_collapse4(const Node *nodes, int64_t n, int32_t copies, const WinFra
                       CNode4 *out, unsigned int *err, hipStream_t st,
                       const uint8_t *inside = nullptr);
 // Per-instance bounds of u dt of a target beam from its statistics (window copies); with the
-// query beam's statistics, its shear and the bounds of the sheared motion.
-void launch_win_bounds(const InstStats *stats, int32_t n_inst, double dt,
-                       const InstStats *q_stats, WinBound *vb, hipStream_t st);
+// query beam's statistics, its shear (reach: the time of a descent) and the bounds of the sheared
+// motion.
+void launch_win_bounds(const InstStats *stats, const BeamDev &b, double dt, const InstStats *q_stats,
+                       double reach, WinBound *vb, hipStream_t st);
 // Nodes of the b.m steps of view b sharing the shape over its b.n rows, each step's
 // leaf boxes computed from the photons (sorted_rows: row of each sorted position;
 // flags: b.m (b.n - 1) arrival flags, zero on entry and left zero (the second arrival at
