@@ -387,9 +387,9 @@ typedef struct {
 } tril_st_table;
 
 /* Exact ST yields for steps k0 .. k0+n_steps-1: clouds of the target beam in a
- * hierarchy per step (boxes of edges `cell` about the mid-step positions), clouds of the
- * query beam descending it, Y evaluated in FP64 for every overlapping pair and added to
- * the table under (q_bins[i], t_bins[j]). Bins are per caller row (from tril_st_bin);
+ * hierarchy per window of up to 32 steps (boxes of edges `cell`, swept from the window's first
+ * mid-step to its last), clouds of the query beam descending it, Y evaluated in FP64 for every
+ * overlapping pair and step and added to the table under (q_bins[i], t_bins[j]). Bins are per caller row (from tril_st_bin);
  * pairs with a negative bin are skipped. *total (host) receives the sum of all yields.
  * Synchronous. TRIL_E_OVERFLOW if the table filled up; TRIL_E_DATA for invalid photon
  * data; TRIL_E_INVAL for bad arguments (cell not finite and > 0, cap not a power of two,

@@ -1699,8 +1699,8 @@ int st_window(tril_ctx *c, const tril_beam *t, const tril_beam *q, const double 
     }
 }
 
-// Statistical-regime pass over steps k0 .. k0+n_steps-1 (asynchronous, but for st_window): clouds of edges
-// `cell` in a hierarchy per window of steps, yields (or by `mode` overlap integrals,
+// Statistical-regime pass over steps k0 .. k0+n_steps-1 (asynchronous, but for st_window): clouds
+// of edges `cell` in a hierarchy per window of steps, yields (or by `mode` overlap integrals,
 // exposures, meetings) added to the table under (q_bins[i], t_bins[j]) or the cloud pair;
 // with a filter set, only its keys. Per-wave sums go to c->st_slots (cleared here together
 // with the table).

@@ -372,7 +372,8 @@ __device__ __forceinline__ void photon_box(const RowPhoton &r, double t, double 
 // enters no result); classes in the target tree make it reach further for every query of mixed
 // energies. Beams of 1.6e7 photons with E^-2 spectra: 398 -> 373 ms per run; above the 4 to 9
 // lowest bits 0.3% apart, above 13 or more and with three bits 1% and more slower. Where the
-// two beams' largest energies give y < 64 most pairs are above threshold: plain codes.
+// two beams' largest energies give y < 64 most pairs are above threshold: plain codes. Runs of
+// several instances keep plain codes too: what classes give there has not been measured.
 constexpr int kClassBits = 2, kClassLow = 9;
 __device__ __forceinline__ uint32_t class_code(uint32_t code, int bits, double E,
                                                const InstStats &t, const InstStats &self) {

@@ -198,7 +198,7 @@ __global__ void k_mlp_reduce(const float *__restrict__ out, int64_t n, int K, fl
 // and a launch per member 1.49 ms (713 TFLOP/s), 80 rows and one launch for all of them 1.33 ms
 // (797); 64 rows 1.39 (each weight fragment feeds fewer products), 96 rows at two workgroups
 // 1.57, 64 rows at four 1.55 (registers spill).
-// Same rounding points as the layer-by-layer path (input, every hidden activation to BF16,
+// Same rounding points as in training (input, every hidden activation to BF16,
 // FP32 accumulation); the activation uses the hardware exponential and reciprocal.
 constexpr int kFR = 80;                  // rows per workgroup
 constexpr int kHL = kMlpHidden + 8;      // LDS row stride of the activations (BF16), padded

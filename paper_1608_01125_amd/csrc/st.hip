@@ -11,12 +11,14 @@
 // reactivity gives for two photons; sigma = 0 at and below threshold.
 // Evaluation order: ((((w_i w_j) / (V V)) sigma) (1 - u_i.u_j)) dt V_ov.
 //
-// Broad phase: the clouds' boxes at mid-step (rounded outward) in the same hierarchy as
-// the exact path; the traversal evaluates Y in FP64 at every overlapping leaf and adds it
-// to a bin-pair table: key = bin(query) * n_target_bins + bin(target), open addressing
-// with linear probing, keys claimed by compare-and-swap, values added atomically. A lane
-// keeps a running sum while consecutive leaves fall in the same bin pair (neighbouring
-// leaves in Morton order usually share their cell) and adds it to the table once.
+// Broad phase: the clouds' boxes, swept from the first to the last mid-step of a window of up to
+// 32 steps (rounded outward), in the same hierarchy as the exact path. A wave descends it once for
+// eight neighbouring queries, queues the pairs whose boxes meet and sums Y in FP64 over the
+// window's steps in which the two clouds overlap (k_st_traverse); sparse clouds that move many
+// edges per step descend step by step, a lane per query (k_st_lanes). The sums go to a bin-pair
+// table: key = bin(query) * n_target_bins + bin(target), open addressing with linear probing,
+// keys claimed by compare-and-swap, values added atomically, neighbouring pairs of one key first
+// added up across the wave.
 //
 // Depletion (the rate equation of Sec. 2.2 with the loss of collision partners): in
 // exposure mode the traversal adds, per cloud pair (key = i * n_target + j), the pair's
@@ -338,7 +340,8 @@ constexpr int64_t kStLaunch = (int64_t)1 << 25;
 // a descent and an evaluation per step, 2.4 ms with one lane per query and window of 16 steps
 // (each with a descent of its own), 1.8 ms with 16 queries per wave. Four waves per SIMD (128
 // VGPRs, some of the pair code's constants spilled) against two unspilled: 9.5 against 9.8 ms
-// for the rows; five: 11.0 ms.
+// for the rows; five: 11.0 ms. (The rows' times include about 4.5 ms of allocations and row forming
+// that have gone since; they take 3.95 ms now.)
 __global__ void __launch_bounds__(64, 4) k_st_traverse(
     const Node *__restrict__ nodes, int32_t n_int, const PBox *__restrict__ root_box,
     const PBox *__restrict__ qbox, const uint32_t *__restrict__ qorder, int64_t nq, int64_t groups,
@@ -722,11 +725,11 @@ __global__ void __launch_bounds__(256) k_st_deplete(long long *__restrict__ pkey
 // definition's own positions (below 1e-15 M) is what a decision has to clear: pairs within
 // `band` of r^2, and pairs whose approach the window cuts off, take swarm_hit itself. The
 // counts are therefore the definition's.
-// 24 x 24 swarms of 4096 real photons: 2.45 ms per call, pair finding included, against 184 ms
-// with one lane per photon walking the octree down to every colliding photon, six FP64
+// 24 x 24 swarms of 4096 real photons: 2.2 to 2.3 ms per call, pair finding included, against
+// 184 ms with one lane per photon walking the octree down to every colliding photon, six FP64
 // divisions per node. Bound by FP64 issue in the pair loop (5.2 ms while each photon pair
-// branched on the band by itself); four waves per SIMD (128 VGPRs) against two unspilled:
-// 5.2 against 7.7 ms then, five 2.6 ms and six 4.8 ms now.
+// branched on the band by itself); four waves per SIMD (128 VGPRs) against two unspilled: 5.2
+// against 7.7 ms then; five and six 2.6 and 4.8 ms where four took 2.45.
 constexpr int64_t kSwarmMax = (int64_t)1 << 30;  // real photons per macro-particle
 
 __device__ __forceinline__ int swarm_level(int64_t n) {

@@ -644,7 +644,6 @@ void launch_st_mask_bins(const int32_t *bins, int64_t n, const uint8_t *mark, in
                          hipStream_t st);
 void launch_fill_keys(long long *p, int64_t n, hipStream_t st);
 void launch_st_clear(long long *keys, double *vals, int64_t cap, double *slots, hipStream_t st);
-// Arguments as for launch_traverse.
 // Depletion pass over the cloud-pair table (pkeys = i * t.n + j, pvals = exposure): every
 // pair's exposure becomes its depleted yield, which is added to the bin-pair table
 // (keys/vals, cap a power of two) under (q_bins[i], t_bins[j]); totals into slots.
